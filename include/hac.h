@@ -252,22 +252,26 @@ const char *hac_last_error(const hac_ctx *ctx);
  *                        groups of two or more workgroups (the default; a
  *                        workgroup alone does better rescanning at once),
  *                        2 = also on one workgroup.
- *   HAC_OPT_ROUNDS       hac_run, single and complete linkage: merge in rounds
- *                        instead of one pair per step.  Each round merges every
+ *   HAC_OPT_ROUNDS       hac_run, all linkages but centroid: merge in rounds
+ *                        instead of one pair per step; the records come out in
+ *                        the order of Section 4's loop, byte-identical to it.
+ *                        Single and complete linkage: each round merges every
  *                        pair of clusters that are each other's nearest
  *                        neighbour under the key order (D, i, j) (single
  *                        linkage: the globally closest pair, plus those whose
  *                        distance is the only minimum of both rows), applies
  *                        all their updates at once and rescans the rows that
- *                        need it; the records come out in the order of Section
- *                        4's loop, byte-identical to it.  0 = never, 1 = for
- *                        n >= 1024 (the default; the remaining merges go to the
- *                        one-merge-per-step kernel once rounds merge few pairs
- *                        each: near the end of a run, and early for single
- *                        linkage on input with many equal values), 2 = always,
- *                        rounds to the end.  Not
- *                        used by hac_run_noalloc, HAC_MODE_SCAN or other
- *                        linkages.
+ *                        need it.  Group average, weighted average, Ward: each
+ *                        round makes the merges that the one-merge-per-step
+ *                        loop would make next, as many as the rows' two smallest
+ *                        entries prove to come next (hac_stats.rounds and
+ *                        handed_over are 0 then).  0 = never, 1 = for n >= 1024
+ *                        (n >= 192 for the averaging linkages; the default; the
+ *                        remaining merges go to the one-merge-per-step kernel
+ *                        once rounds merge few pairs each: near the end of a
+ *                        run, and early on input with many equal values),
+ *                        2 = always, rounds to the end.  Not used by
+ *                        hac_run_noalloc, HAC_MODE_SCAN or centroid linkage.
  *   HAC_OPT_INJECT_STALL failure test: 1 = in every following hac_run that runs
  *                        on several workgroups, workgroup 0 never publishes its
  *                        first exchange, so the other workgroups' bounded waits
