@@ -37,6 +37,8 @@ GOLDEN = os.path.join(ROOT, "tests", "golden", "oracle_digests.json")
 CSRC = os.path.join(ROOT, "paper_1709_06816_amd", "csrc")
 # Counter profiles: kernel -> (file, sources whose hash the counters were taken on).
 PROFILES = {
+    "k_contract": ("k_contract_rmsd_like_n32768_pmc.md", ["hac_contract.hip", "hac_contract.h", "hac_dev.h",
+                                                          "hac_engine.h"]),
     "k_rounds": ("k_rounds_rmsd_like_n32768_pmc.md", ["hac_rounds.hip", "hac_rounds.h", "hac_dev.h",
                                                       "hac_engine.h"]),
     "k_scan": ("k_scan_rmsd_like_n32768_pmc.md", ["hac_scan.hip", "hac_scan.h", "hac_dev.h"]),
@@ -643,9 +645,15 @@ def main():
     rounds_ms = float(np.mean(rms))
     # The round engine's kernel alone (HIP events around its launch): its own
     # updated and rescanned entries, and the records of its merges.
-    ab = alg_bytes_merge(n, {"update_elems": stats["rounds_update_elems"],
-                             "rescan_elems": stats["rounds_rescan_elems"]})
-    traffic, traffic_src = measured_traffic("k_rounds", n)
+    # Up to n = 32768 that is the contraction kernel, whose counter is the
+    # entries it reads and writes (the matrix of every round, once each); above,
+    # the in-place kernel.
+    contract = n <= 32768
+    kernel = "k_contract" if contract else "k_rounds"
+    ab = 4.0 * stats["rounds_rescan_elems"] + 16.0 * (n - 1) if contract else \
+        alg_bytes_merge(n, {"update_elems": stats["rounds_update_elems"],
+                            "rescan_elems": stats["rounds_rescan_elems"]})
+    traffic, traffic_src = measured_traffic(kernel, n)
     gold = golden("rmsd_like_n32768_complete") if n == 32768 else None
     log("step %.1f ms, merge kernels %.1f ms, %d rounds" % (ms_step, kernel_ms, stats["rounds"]))
 
@@ -668,9 +676,9 @@ def main():
         "dendrogram_s": ms_step / 1000.0,
         "full_list_identical_to_oracle": None if gold is None else records_sha(rec) == gold["records_sha256"],
         "roofline": roofline(ab, rounds_ms, traffic, traffic_src,
-                             "k_rounds (rounds of reciprocal-nearest-neighbour merges)",
+                             "%s (rounds of reciprocal-nearest-neighbour merges)" % kernel,
                              {"merge_phase_ms": kernel_ms,
-                              "merge_phase_note": "k_rounds, the one-merge-per-step kernel that takes over for "
+                              "merge_phase_note": "that kernel, the one-merge-per-step kernel that takes over for "
                                                   "the last merges, and the record sort",
                               "workgroups": stats["workgroups"], "rounds": stats["rounds"],
                               "handed_over": bool(stats["handed_over"]), "rescans": stats["rescans"],

@@ -265,11 +265,11 @@ const char *hac_last_error(const hac_ctx *ctx);
  *                        round makes the merges that the one-merge-per-step
  *                        loop would make next, as many as the rows' two smallest
  *                        entries prove to come next (hac_stats.rounds and
- *                        handed_over are 0 then).  0 = never, 1 = for n >= 1024
- *                        (n >= 192 for the averaging linkages; the default; the
- *                        remaining merges go to the one-merge-per-step kernel
- *                        once rounds merge few pairs each: near the end of a
- *                        run, and early on input with many equal values),
+ *                        handed_over are 0 then).  0 = never, 1 = for n >= 64
+ *                        (complete), 192 (averaging linkages) or 200 (single;
+ *                        the default; the remaining merges go to the
+ *                        one-merge-per-step kernel once rounds merge few pairs
+ *                        each, on input with many equal values),
  *                        2 = always, rounds to the end.  Not used by
  *                        hac_run_noalloc, HAC_MODE_SCAN or centroid linkage.
  *   HAC_OPT_INJECT_STALL failure test: 1 = in every following hac_run that runs
@@ -313,7 +313,10 @@ int hac_set_option(hac_ctx *ctx, int32_t option, int64_t value);
  *   kernel_ms:         device time of the merge kernel (HIP events on the run's stream)
  *   init_ms:           device time of the set-up kernels before it
  *   rescans:           rows whose cached minimum was recomputed
- *   rescan_elems:      matrix entries read by those recomputations
+ *   rescan_elems:      matrix entries read by those recomputations (rounds of
+ *                      single and complete linkage up to n = 32768: the
+ *                      entries that the rounds' matrices were read and written
+ *                      with, rounds_rescan_elems likewise)
  *   update_elems:      (k) entries updated by the Lance-Williams step, summed over merges
  *   workgroups:        workgroups the merge kernel ran with
  *   block:             threads per workgroup

@@ -12,6 +12,7 @@
 #include <vector>
 
 #include "hac.h"
+#include "hac_contract.h"
 #include "hac_ctx_info.h"
 #include "hac_engine.h"
 #include "hac_order.h"
@@ -26,7 +27,10 @@ constexpr size_t kAlign = 256;
 constexpr int kDefaultSingleWgN = 1536;
 constexpr int kDeferMinGroup = 2;       // HAC_OPT_DEFER = 1: defer from this many workgroups on
 constexpr int64_t kDefaultTimeoutMs = 10000;
-constexpr int kRoundsMinN = 1024;       // HAC_OPT_ROUNDS = 1: rounds of merges from this n on
+// HAC_OPT_ROUNDS = 1: rounds of merges from this n on.  Measured against one
+// merge per step on one workgroup: complete n=64 0.15 / 0.18 ms, n=512 0.25 /
+// 1.65; single n=150 0.43 / 0.41 (tied input), n=300 0.59 / 0.85.
+constexpr int kRoundsMinComplete = 64, kRoundsMinSingle = 200;
 constexpr int kOrderMinN = 192;         // the same for the ordered rounds of the averaging linkages (n=200: 0.57 ms
                                         // against 0.65 one merge per step, n=100: 0.36 against 0.29)
 
@@ -721,7 +725,9 @@ int plan_seq(hac_ctx *c, int32_t n, uint32_t flags, bool noalloc, int *g_out, in
 // hac_run through the round engine (single and complete linkage).
 int run_rounds(hac_ctx *c, float *dist, int32_t n, int32_t linkage, hac_merge *out, uint32_t flags, hipStream_t s) {
     if (!c->coop) return fail(c, HAC_EDEVICE, "device does not support cooperative launch");
-    int G = c->cus * hac::rounds_occupancy();
+    // On a shrinking matrix where a row fits a workgroup, in place above.
+    const bool contract = n <= hac::kContractMaxN && hac::contract_occupancy(linkage) > 0;
+    int G = c->cus * (contract ? 1 : hac::rounds_occupancy());
     if (c->opt_wgs > 0) G = std::min(G, (int)c->opt_wgs);
     // Automatic mode: the one-merge-per-step kernel is queued behind the
     // round engine and makes the remaining merges if the round engine hands
@@ -740,8 +746,10 @@ int run_rounds(hac_ctx *c, float *dist, int32_t n, int32_t linkage, hac_merge *o
     const size_t st_off = ctl_bytes, st_bytes = kAlign;
     const size_t rk_off = st_off + st_bytes, rk_bytes = align_up((size_t)n * 8, kAlign);
     const size_t ro_off = rk_off + rk_bytes;
-    const hac::RoundsLayout Lo = hac::rounds_layout(n, G);
-    const size_t sl_off = ro_off + Lo.bytes;
+    const hac::RoundsLayout Lr = hac::rounds_layout(n, G);
+    const hac::ContractLayout Lc = hac::contract_layout(n);
+    const size_t zero_bytes = contract ? Lc.zero_bytes : Lr.zero_bytes;
+    const size_t sl_off = ro_off + (contract ? Lc.bytes : Lr.bytes);
     const size_t sl_bytes = (handover && g > 1) ? (size_t)2 * (g + 1) * hac::kSlotStride * 8 : 0;
     rc = ensure_dev(c, &c->ws, &c->ws_cap, sl_off + sl_bytes, "workspace");
     if (rc) return rc;
@@ -773,32 +781,38 @@ int run_rounds(hac_ctx *c, float *dist, int32_t n, int32_t linkage, hac_merge *o
     inst.link = linkage;
     HIP_TRY(c, hipEventRecord(c->ev[0], s));
     HIP_TRY(c, hac::launch_zero(ws, (st_off + st_bytes) / 4, s));
-    HIP_TRY(c, hac::launch_zero(ws + ro_off + Lo.ctl, sizeof(hac::RoundsCtl) / 4, s));
+    HIP_TRY(c, hac::launch_zero(ws + ro_off, zero_bytes / 4, s));
     if (sl_bytes) HIP_TRY(c, hac::launch_zero(ws + sl_off, sl_bytes / 4, s));
     HIP_TRY(c, hac::launch_setup(inst, dist, s));
     HIP_TRY(c, hipEventRecord(c->ev[1], s));
     const int rflags = (c->opt_profile ? hac::kFlagProfile : 0) | (handover ? 0 : hac::kFlagNoHandover) |
                        (c->opt_stall ? hac::kFlagStall : 0);
     hac::Control *ctl = reinterpret_cast<hac::Control *>(ws);
-    hipError_t e = hac::launch_rounds(D, n, linkage, inst.status, ctl, ws + ro_off, G, timeout_ticks(c), rflags, s);
+    hipError_t e = contract ? hac::launch_contract(D, n, linkage, inst.status, ctl, ws + ro_off, G, timeout_ticks(c),
+                                                   rflags, s)
+                            : hac::launch_rounds(D, n, linkage, inst.status, ctl, ws + ro_off, G, timeout_ticks(c),
+                                                 rflags, s);
     if (e != hipSuccess) return hip_fail(c, e, "round kernel launch");
     HIP_TRY(c, hipEventRecord(c->ev[3], s));
     if (handover) {
         // Resumes from the round engine's state if it hands over; its
         // records join the round engine's before they are sorted.
         hac::Instance seq = inst;
-        seq.out = hac::rounds_records(n, G, ws + ro_off);
+        seq.out = reinterpret_cast<hac_merge *>(ws + ro_off + (contract ? Lc.rec : Lr.rec));
         seq.slots = reinterpret_cast<uint64_t *>(ws + sl_off);
         seq.exchange = (int32_t)c->opt_exchange;
         seq.flags = seq_flags | hac::kFlagAfterRounds;
-        e = hac::launch_merge(seq, g, block, ctl, timeout_ticks(c), s, hac::rounds_resume(n, G, ws + ro_off));
+        e = hac::launch_merge(seq, g, block, ctl, timeout_ticks(c), s,
+                              contract ? hac::contract_resume(n, ws + ro_off) : hac::rounds_resume(n, G, ws + ro_off));
         if (e != hipSuccess) return hip_fail(c, e, "merge kernel launch");
     }
-    e = hac::launch_rank(n, dev_out, inst.status, ctl, ws + ro_off, G, s);
+    e = hac::launch_rank(n, dev_out, inst.status, ctl, ws + ro_off + (contract ? Lc.rec : Lr.rec),
+                         reinterpret_cast<const uint64_t *>(ws + ro_off + (contract ? Lc.key : Lr.key)),
+                         reinterpret_cast<uint32_t *>(ws + ro_off + (contract ? Lc.rank : Lr.rank)), s);
     if (e != hipSuccess) return hip_fail(c, e, "record sort launch");
     HIP_TRY(c, hipEventRecord(c->ev[2], s));
     c->pending_wgs = G;
-    c->pending_block = hac::kRoundsBlock;
+    c->pending_block = contract ? hac::kContractBlock : hac::kRoundsBlock;
     c->pending_group = G;
     c->pending_graph = 0;
     c->pending_plan_source = c->pending_plan_share = c->pending_plan_upd = 0;
@@ -983,7 +997,8 @@ int run_impl(hac_ctx *c, float *dist, int32_t n, int32_t linkage, hac_merge *out
     c->pending_scan = false;
     if (n == 1) return HAC_OK;
     if (!noalloc && !(flags & HAC_MODE_SCAN) && (linkage == HAC_SINGLE || linkage == HAC_COMPLETE) &&
-        (c->opt_rounds == 2 || (c->opt_rounds == 1 && n >= kRoundsMinN)))
+        (c->opt_rounds == 2 ||
+         (c->opt_rounds == 1 && n >= (linkage == HAC_SINGLE ? kRoundsMinSingle : kRoundsMinComplete))))
         return run_rounds(c, dist, n, linkage, out, flags, s);
     if (!noalloc && (flags & HAC_MODE_SCAN)) return run_scan(c, dist, n, linkage, out, flags, s);
     if (!noalloc && (linkage == HAC_AVERAGE || linkage == HAC_WEIGHTED || linkage == HAC_WARD) &&

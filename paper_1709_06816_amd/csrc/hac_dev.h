@@ -94,6 +94,42 @@ __device__ __forceinline__ uint64_t wave_min(uint64_t v) { return __ockl_wfred_m
 __device__ __forceinline__ unsigned long long wave_sum(unsigned long long v) { return __ockl_wfred_add_u64(v); }
 
 
+// Wave reductions by DPP: within quads (xor 1, xor 2), half rows, rows, then
+// rows 0 and 2 into 1 and 3 and row 1 into rows 2 and 3; the result is in
+// lane 63.  Call with every lane of the wave active.
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint32_t dpp32(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_update_dpp((int)v, (int)v, CTRL, ROW_MASK, 0xF, false);
+}
+template <int CTRL, int ROW_MASK>
+__device__ __forceinline__ uint64_t dpp64(uint64_t v) {
+    return ((uint64_t)dpp32<CTRL, ROW_MASK>((uint32_t)(v >> 32)) << 32) | dpp32<CTRL, ROW_MASK>((uint32_t)v);
+}
+__device__ __forceinline__ uint32_t last_min32(uint32_t v) {
+    v = min(v, dpp32<0xB1, 0xF>(v));
+    v = min(v, dpp32<0x4E, 0xF>(v));
+    v = min(v, dpp32<0x141, 0xF>(v));
+    v = min(v, dpp32<0x140, 0xF>(v));
+    v = min(v, dpp32<0x142, 0xA>(v));
+    return min(v, dpp32<0x143, 0xC>(v));
+}
+__device__ __forceinline__ uint64_t last_min64(uint64_t v) {
+    v = umin64(v, dpp64<0xB1, 0xF>(v));
+    v = umin64(v, dpp64<0x4E, 0xF>(v));
+    v = umin64(v, dpp64<0x141, 0xF>(v));
+    v = umin64(v, dpp64<0x140, 0xF>(v));
+    v = umin64(v, dpp64<0x142, 0xA>(v));
+    return umin64(v, dpp64<0x143, 0xC>(v));
+}
+__device__ __forceinline__ uint32_t wave_min32(uint32_t v) {
+    return (uint32_t)__builtin_amdgcn_readlane((int)last_min32(v), 63);
+}
+__device__ __forceinline__ uint64_t wave_min64(uint64_t v) {
+    v = last_min64(v);
+    return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), 63) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63);
+}
+
 // Grid barrier of a cooperative launch of G workgroups: every workgroup's
 // writes before it are visible to every workgroup after it (stores complete,
 // then an agent-scope release, a monotonic arrival counter *bar, an

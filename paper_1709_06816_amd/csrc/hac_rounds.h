@@ -26,7 +26,9 @@ struct RoundsCtl {
 // Device workspace of one round-engine run on an n-item instance with G
 // workgroups; offsets in bytes from the workspace base (256-byte aligned).
 struct RoundsLayout {
-    size_t ctl, rk, cnt, size, role, resc, pairs, k1, rec, key, live, bytes;
+    size_t ctl, rank;    // cleared before a launch: zero_bytes from the start
+    size_t zero_bytes;
+    size_t rk, cnt, size, role, resc, pairs, k1, rec, key, live, bytes;
 };
 RoundsLayout rounds_layout(int n, int G);
 
@@ -53,14 +55,10 @@ hipError_t launch_rounds(float *D, int n, int link, uint32_t *status, Control *c
 // Hand-over state inside a round-engine workspace (for launch_merge).
 Resume rounds_resume(int n, int G, void *ws);
 
-// Records of the workspace (round engine, then any kernel it handed over
-// to) written to `out` in merge order.
-// Nothing is written if the launch failed (status or ctl->error set).
-hipError_t launch_rank(int n, hac_merge *out, const uint32_t *status, const Control *ctl, void *ws, int G,
-                       hipStream_t stream);
-
-// Record array of the workspace (the kernel queued behind the round engine
-// writes its records there).
-hac_merge *rounds_records(int n, int G, void *ws);
+// The n-1 records `rec` (16 bytes each, device) with sort keys `key` written to
+// `out` in key order; `rank`: n words, zero.  Nothing is written if the launch
+// failed (status or ctl->error set).
+hipError_t launch_rank(int n, hac_merge *out, const uint32_t *status, const Control *ctl, const void *rec,
+                       const uint64_t *key, uint32_t *rank, hipStream_t stream);
 
 }  // namespace hac
