@@ -19,6 +19,7 @@
 #include "hac_rmsd.h"
 #include "hac_rounds.h"
 #include "hac_scan.h"
+#include "hac_small.h"
 #include "hac_validate.h"
 
 namespace {
@@ -30,6 +31,7 @@ constexpr int64_t kDefaultTimeoutMs = 10000;
 // HAC_OPT_ROUNDS = 1: rounds of merges from this n on.  Measured against one
 // merge per step on one workgroup: complete n=64 0.15 / 0.18 ms, n=512 0.25 /
 // 1.65; single n=150 0.43 / 0.41 (tied input), n=300 0.59 / 0.85.
+constexpr int kSmallComplete = 144;     // complete linkage: the small-instance kernel up to this n
 constexpr int kRoundsMinComplete = 64, kRoundsMinSingle = 200;
 constexpr int kOrderMinN = 192;         // the same for the ordered rounds of the averaging linkages (n=200: 0.57 ms
                                         // against 0.65 one merge per step, n=100: 0.36 against 0.29)
@@ -71,6 +73,8 @@ struct hac_ctx {
     size_t dout_cap = 0;         // records
     void *pinned = nullptr;      // host staging (status read-back, descriptor upload)
     size_t pinned_cap = 0;
+    void *recs = nullptr;        // host staging of merge records
+    size_t recs_cap = 0;
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};  // [3]: end of the round engine's kernel
 
     hac_stats stats{};
@@ -171,6 +175,22 @@ int ensure_pinned(hac_ctx *c, size_t need) {
     return HAC_OK;
 }
 
+// Page-locked room for merge records (grown on demand, up to kStagedRecords).
+constexpr size_t kStagedRecords = (size_t)2 << 20;
+int ensure_records(hac_ctx *c, size_t need) {
+    if (need <= c->recs_cap) return HAC_OK;
+    void *p = nullptr;
+    const size_t sz = std::min(kStagedRecords, std::max(need, (size_t)65536));
+    if (hipHostMalloc(&p, sz, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        return HAC_ENOMEM;
+    }
+    if (c->recs) (void)hipHostFree(c->recs);  // idle: every copy into it is waited for
+    c->recs = p;
+    c->recs_cap = sz;
+    return HAC_OK;
+}
+
 int set_device(hac_ctx *c) {
     HIP_TRY(c, hipSetDevice(c->device));
     return HAC_OK;
@@ -265,11 +285,20 @@ int finish(hac_ctx *c, hipStream_t s, int nstatus, hac_merge *out, size_t nrec, 
     c->pending_stream = s;
     c->pending_count = nstatus;
     if (flags & HAC_OUT_DEVICE) return HAC_OK;
+    // The records come back beside the status word, through page-locked memory
+    // where there are not too many of them: one wait instead of two (n=100:
+    // 25 us less), and on an error out stays as it was.
+    const size_t rec_bytes = nrec * sizeof(hac_merge);
+    const bool staged = nrec && rec_bytes <= kStagedRecords && ensure_records(c, rec_bytes) == HAC_OK;
+    if (staged) HIP_TRY(c, hipMemcpyAsync(c->recs, c->dout, rec_bytes, hipMemcpyDeviceToHost, s));
     HIP_TRY(c, hipStreamSynchronize(s));
     c->pending = false;
     int rc = check_status(c);
     if (rc != HAC_OK) return rc;
-    if (nrec) HIP_TRY(c, hipMemcpy(out, c->dout, nrec * sizeof(hac_merge), hipMemcpyDeviceToHost));
+    if (staged)
+        std::memcpy(out, c->recs, rec_bytes);
+    else if (nrec)
+        HIP_TRY(c, hipMemcpy(out, c->dout, rec_bytes, hipMemcpyDeviceToHost));
     return HAC_OK;
 }
 
@@ -548,6 +577,11 @@ int hac_create(int device, hac_ctx **out) {
         return HAC_EDEVICE;
     }
     c->lds_max = usable;
+    if (hac::small_setup() != hipSuccess) {
+        (void)hipGetLastError();
+        hac_destroy(c);
+        return HAC_EDEVICE;
+    }
     // The allocation-free entry point's scratch: this device's copy of the
     // library's static array (the device is current), and the page-locked
     // word its status comes back through.
@@ -576,6 +610,7 @@ int hac_destroy(hac_ctx *c) {
     if (c->rmsd_ws) (void)hipFree(c->rmsd_ws);
     if (c->dout) (void)hipFree(c->dout);
     if (c->pinned) (void)hipHostFree(c->pinned);
+    if (c->recs) (void)hipHostFree(c->recs);
     for (auto &e : c->ev)
         if (e) (void)hipEventDestroy(e);
     if (c->own) (void)hipStreamDestroy(c->own);
@@ -978,6 +1013,40 @@ int run_scan(hac_ctx *c, float *dist, int32_t n, int32_t linkage, hac_merge *out
     return finish(c, s, 1, out, (flags & HAC_OUT_DEVICE) ? 0 : (size_t)(n - 1), flags, ws);
 }
 
+// hac_run of a small instance: one workgroup, the matrix in its LDS.  The
+// caller's matrix is only read.
+int run_small(hac_ctx *c, const float *dist, int32_t n, int32_t linkage, hac_merge *out, uint32_t flags,
+              hipStream_t s) {
+    const size_t ctl_bytes = align_up(sizeof(hac::Control), kAlign);
+    int rc = ensure_dev(c, &c->ws, &c->ws_cap, ctl_bytes + kAlign, "workspace");
+    if (rc) return rc;
+    rc = ensure_pinned(c, ctl_bytes + kAlign);
+    if (rc) return rc;
+    hac_merge *dev_out = out;
+    if (!(flags & HAC_OUT_DEVICE)) {
+        size_t cap_bytes = c->dout_cap * sizeof(hac_merge);
+        rc = ensure_dev(c, reinterpret_cast<void **>(&c->dout), &cap_bytes, (size_t)(n - 1) * sizeof(hac_merge),
+                        "merge buffer");
+        if (rc) return rc;
+        c->dout_cap = cap_bytes / sizeof(hac_merge);
+        dev_out = c->dout;
+    }
+    char *ws = reinterpret_cast<char *>(c->ws);
+    HIP_TRY(c, hipEventRecord(c->ev[0], s));
+    HIP_TRY(c, hipEventRecord(c->ev[1], s));
+    hipError_t e = hac::launch_small(dist, n, linkage, dev_out, reinterpret_cast<uint32_t *>(ws + ctl_bytes),
+                                     reinterpret_cast<hac::Control *>(ws), s);
+    if (e != hipSuccess) return hip_fail(c, e, "small-instance kernel launch");
+    HIP_TRY(c, hipEventRecord(c->ev[2], s));
+    c->pending_wgs = 1;
+    c->pending_block = hac::kRunBlock;
+    c->pending_group = 1;
+    c->pending_graph = 0;
+    c->pending_plan_source = c->pending_plan_share = c->pending_plan_upd = 0;
+    c->pending_deferred = 1;
+    return finish(c, s, 1, out, (flags & HAC_OUT_DEVICE) ? 0 : (size_t)(n - 1), flags, ws);
+}
+
 // hac_run and hac_run_noalloc.  noalloc: the device scratch is the static
 // array (c->scratch) instead of the context's workspace, the merge kernel
 // runs on at most HAC_NOALLOC_MAX_WORKGROUPS workgroups, out is device
@@ -996,6 +1065,12 @@ int run_impl(hac_ctx *c, float *dist, int32_t n, int32_t linkage, hac_merge *out
     c->pending_rounds = false;
     c->pending_scan = false;
     if (n == 1) return HAC_OK;
+    // Small instances, unless an option asks for another split of the work
+    // (whole call, small kernel / otherwise: average n=100 149 / 358 us, n=192
+    // 307 / 700; complete n=100 148 / 226, n=150 242 / 230).
+    if (!noalloc && !(flags & HAC_MODE_SCAN) && n <= (linkage == HAC_COMPLETE ? kSmallComplete : hac::kSmallMaxN) && c->opt_rounds == 1 && c->opt_defer == 1 &&
+        !c->opt_wgs && !c->opt_single_n && !c->opt_block && !c->opt_profile)
+        return run_small(c, dist, n, linkage, out, flags, s);
     if (!noalloc && !(flags & HAC_MODE_SCAN) && (linkage == HAC_SINGLE || linkage == HAC_COMPLETE) &&
         (c->opt_rounds == 2 ||
          (c->opt_rounds == 1 && n >= (linkage == HAC_SINGLE ? kRoundsMinSingle : kRoundsMinComplete))))
@@ -1181,7 +1256,7 @@ int hac_batch(hac_ctx *c, float *packed, const int64_t *offsets, const int32_t *
         // One executable graph per layout; descriptors are re-read from the
         // pinned buffer at every launch.
         char key[256];
-        snprintf(key, sizeof key, "%p:%zu:%zu:%zu:%zu:%d:%d:%d:%d:%zu:%llu", c->ws, B.in_off, B.up_bytes, B.st_off + B.st_bytes,
+        snprintf(key, sizeof key, "%p:%p:%zu:%zu:%zu:%zu:%d:%d:%d:%d:%zu:%llu", c->ws, c->pinned, B.in_off, B.up_bytes, B.st_off + B.st_bytes,
                  B.sl_bytes, B.L.count, B.L.ngroups, B.L.block * 16 + B.L.upd, B.L.grid, B.L.lds,
                  (unsigned long long)timeout_ticks(c));
         auto it = c->graphs.find(key);
