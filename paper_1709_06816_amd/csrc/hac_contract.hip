@@ -50,6 +50,7 @@ constexpr int V = 4;                         // the same for in-place updates
 constexpr int kMaxM = kContractMaxN;
 constexpr int kWords = kMaxM / 64;
 constexpr uint64_t kNone = ~0ull;
+constexpr uint32_t kNowhere = 0xFFFFu;       // no column's place
 constexpr uint32_t kIndex = 0x7FFFu;
 constexpr uint32_t kTied = 0x8000u;          // nearest-neighbour entry: the minimum is attained more than once
 constexpr int kWindow = 8;                   // hand-over, as in hac_rounds.hip
@@ -61,7 +62,8 @@ constexpr int kInplaceMin = 1024;            // smaller matrices are contracted 
 static_assert(KE * B == kMaxM && KE == 4 * U, "a row takes one workgroup, four chunks");
 
 // LDS (dynamic), byte offsets.  The row area holds the rows on their way;
-// before the first of a round, the nearest neighbours (2 bytes each).
+// before the first of a round, the nearest neighbours and the columns' places
+// (2 bytes each).
 constexpr uint32_t kRowArea = (kMaxM + 64) * 4;
 constexpr uint32_t oRow = 0;
 constexpr uint32_t oRet = oRow + kRowArea;   // u64 per 64 columns: retired this round
@@ -170,6 +172,19 @@ __device__ __forceinline__ int below(uint64_t kept) {
     return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(kept >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)kept, 0u));
 }
 
+// Inclusive prefix sum over the wave (DPP: shifts within rows, then row ends).
+template <int CTRL, int ROW_MASK> __device__ __forceinline__ int prefix_step(int v) {
+    return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROW_MASK, 0xF, false);
+}
+__device__ __forceinline__ int wave_prefix(int v) {
+    v = prefix_step<0x111, 0xF>(v);
+    v = prefix_step<0x112, 0xF>(v);
+    v = prefix_step<0x114, 0xF>(v);
+    v = prefix_step<0x118, 0xF>(v);
+    v = prefix_step<0x142, 0xA>(v);
+    return prefix_step<0x143, 0xC>(v);
+}
+
 struct Clock {
     bool on;
     uint64_t mark;
@@ -204,6 +219,7 @@ __global__ __launch_bounds__(B) void k_contract(Args A) {
     }
     uint32_t *const row = lds<uint32_t>(oRow);
     uint16_t *const near = lds<uint16_t>(oRow);
+    uint16_t *const goes = lds<uint16_t>(oRow + kMaxM * 2);
     uint64_t *const ret = lds<uint64_t>(oRet), *const sur = lds<uint64_t>(oSur), *const dead = lds<uint64_t>(oDead);
     uint16_t *const pre = lds<uint16_t>(oPre), *const prs = lds<uint16_t>(oPrs);
     float *D = A.D;
@@ -304,15 +320,7 @@ __global__ __launch_bounds__(B) void k_contract(Args A) {
                     sum += cnt[k];
                     ssum += scn[k];
                 }
-                int run = sum, srun = ssum;
-#pragma unroll
-                for (int o = 1; o < 64; o <<= 1) {
-                    const int v = __shfl_up(run, o, 64), sv = __shfl_up(srun, o, 64);
-                    if (lane >= o) {
-                        run += v;
-                        srun += sv;
-                    }
-                }
+                const int run = wave_prefix(sum), srun = wave_prefix(ssum);
                 int at = run - sum, sat = srun - ssum;
 #pragma unroll
                 for (int k = 0; k < 8; ++k) {
@@ -537,21 +545,22 @@ __global__ __launch_bounds__(B) void k_contract(Args A) {
                     st32(reinterpret_cast<uint32_t *>(A.size[out] + kept), (uint32_t)(mg ? sz + A.size[par][b] : sz));
                 }
             }
-            // Where this thread's columns go, the same for every row: kept columns
-            // to their new places, retired ones to their survivors'; columns
-            // retired before go to a word that nothing reads.
+            // Where every column goes, the same for every row: kept columns to
+            // their new places, retired ones to their survivors'; columns retired
+            // before go to a word that nothing reads.  A table beside the nearest
+            // neighbours, from which each thread takes its columns'.
+            for (int c = tid; c < m; c += B) {
+                const uint64_t bit = 1ull << (c & 63), r0 = ret[c >> 6];
+                const int to = (r0 & bit) ? (int)(near[c] & kIndex) : c;
+                goes[c] = (uint16_t)(kCount && (dead[c >> 6] & bit) ? kNowhere : kept_before(to));
+            }
+            __syncthreads();
 #pragma unroll
             for (int k = 0; k < KE; ++k) {
-                if (k % 4 == 0) __builtin_amdgcn_sched_barrier(0);  // few at a time: registers
                 const int c = (k << lt) + t;
-                uint32_t at = (uint32_t)(kMaxM + 32 - grp * stride);
-                if ((k << lt) < m && c < m) {
-                    const uint64_t kept = kCount ? ~(ret[c >> 6] | dead[c >> 6]) : ~ret[c >> 6];
-                    if ((kept >> lane) & 1ull)
-                        at = (uint32_t)((int)pre[c >> 6] + below(kept));
-                    else if (!kCount || !((dead[c >> 6] >> lane) & 1ull))
-                        at = (uint32_t)kept_before((int)(near[c] & kIndex));
-                }
+                uint32_t at = kNowhere;
+                if ((k << lt) < m && c < m) at = goes[c];
+                if (kCount && at == kNowhere) at = (uint32_t)(kMaxM + 32 - grp * stride);
                 if (k & 1)
                     place[k / 2] |= at << 16;
                 else
