@@ -338,7 +338,7 @@ struct BatchLayout {
 // Lay out a batch for `plan`, write its descriptors into the pinned staging
 // buffer and fill `B`.  The caller has validated the batch.  Nothing is
 // enqueued.
-int batch_prepare(hac_ctx *c, float *base, const int64_t *offsets, const int32_t *ns,
+int batch_prepare(hac_ctx *c, float *base, const float *from, const int64_t *offsets, const int32_t *ns,
                   const int32_t *links, int count, hac_merge *dev_out, const int64_t *out_offsets,
                   const BatchPlan &plan, hipStream_t s, BatchLayout *B) {
     std::vector<int32_t> ord(count);
@@ -397,6 +397,7 @@ int batch_prepare(hac_ctx *c, float *base, const int64_t *offsets, const int32_t
     for (int k = 0; k < count; ++k) {
         hac::Instance &I = hin[k];
         I.D = base + offsets[k];
+        I.src = from ? from + offsets[k] : nullptr;
         I.out = dev_out + out_offsets[k];
         I.rowkey = nullptr;
         I.slots = nullptr;
@@ -453,15 +454,11 @@ hipError_t batch_enqueue(hac_ctx *c, const BatchLayout &B, hipStream_t s, hipEve
 // negative value if the plan could not be laid out or launched or if its run
 // reported any error (an instance's status word or the control block); such
 // a plan is never chosen.
-float batch_try_plan(hac_ctx *c, float *scratch, const float *packed, int64_t extent, const int64_t *offsets,
+float batch_try_plan(hac_ctx *c, float *scratch, const float *packed, const int64_t *offsets,
                      const int32_t *ns, const int32_t *links, int count, hac_merge *dev_out,
                      const int64_t *out_offsets, hipStream_t s, const BatchPlan &p) {
-    if (hipMemcpyAsync(scratch, packed, (size_t)extent * 4, hipMemcpyDeviceToDevice, s) != hipSuccess) {
-        (void)hipGetLastError();
-        return -1.0f;
-    }
     BatchLayout B;
-    if (batch_prepare(c, scratch, offsets, ns, links, count, dev_out, out_offsets, p, s, &B) != HAC_OK) return -1.0f;
+    if (batch_prepare(c, scratch, packed, offsets, ns, links, count, dev_out, out_offsets, p, s, &B) != HAC_OK) return -1.0f;
     if (batch_enqueue(c, B, s, c->ev[1]) != hipSuccess || hipEventRecord(c->ev[2], s) != hipSuccess ||
         hipStreamSynchronize(s) != hipSuccess) {
         (void)hipGetLastError();
@@ -504,7 +501,7 @@ int batch_autotune(hac_ctx *c, float *packed, int64_t extent, const int64_t *off
     float best_ms = 1e30f;
     *best = BatchPlan{};
     auto consider = [&](const BatchPlan &p) {
-        const float ms = batch_try_plan(c, scratch, packed, extent, offsets, ns, links, count, dev_out, out_offsets,
+        const float ms = batch_try_plan(c, scratch, packed, offsets, ns, links, count, dev_out, out_offsets,
                                         s, p);
         if (ms >= 0.0f && ms < best_ms) {
             best_ms = ms;
@@ -1126,7 +1123,7 @@ int run_impl(hac_ctx *c, float *dist, int32_t n, int32_t linkage, hac_merge *out
         dev_out = c->dout;
     }
 
-    hac::Instance inst;
+    hac::Instance inst{};
     inst.D = D;
     inst.out = dev_out;
     inst.rowkey = reinterpret_cast<uint64_t *>(ws + rk_off);
@@ -1208,12 +1205,13 @@ int hac_batch(hac_ctx *c, float *packed, const int64_t *offsets, const int32_t *
     c->stats = hac_stats{};
 
     float *base = packed;
+    const float *from = nullptr;  // where the set-ups read, if not in place
     if (flags & HAC_PRESERVE_INPUT) {
         const size_t bytes = (size_t)extent * 4;
         rc = ensure_dev(c, reinterpret_cast<void **>(&c->dcopy), &c->dcopy_cap, bytes, "input copy");
         if (rc) return rc;
-        HIP_TRY(c, hipMemcpyAsync(c->dcopy, packed, bytes, hipMemcpyDeviceToDevice, s));
         base = c->dcopy;
+        from = packed;
     }
     hac_merge *dev_out = out;
     if (!(flags & HAC_OUT_DEVICE)) {
@@ -1239,7 +1237,7 @@ int hac_batch(hac_ctx *c, float *packed, const int64_t *offsets, const int32_t *
             plan = it->second;
             plan_source = 2;
         } else if (c->opt_autotune && count >= 8) {
-            rc = batch_autotune(c, base, extent, offsets, ns, linkages, count, dev_out, out_offsets, s, &plan);
+            rc = batch_autotune(c, packed, extent, offsets, ns, linkages, count, dev_out, out_offsets, s, &plan);
             if (rc) return rc;
             c->plans[sig] = plan;
             plan_source = 1;
@@ -1247,7 +1245,7 @@ int hac_batch(hac_ctx *c, float *packed, const int64_t *offsets, const int32_t *
     }
 
     BatchLayout B;
-    rc = batch_prepare(c, base, offsets, ns, linkages, count, dev_out, out_offsets, plan, s, &B);
+    rc = batch_prepare(c, base, from, offsets, ns, linkages, count, dev_out, out_offsets, plan, s, &B);
     if (rc) return rc;
     HIP_TRY(c, hipEventRecord(c->ev[0], s));
     int graphed = 0;

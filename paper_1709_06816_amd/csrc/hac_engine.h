@@ -59,6 +59,7 @@ struct Instance {
     uint64_t *rowkey;    // n first row minima from the set-up kernel (single-instance path)
     uint64_t *slots;     // exchange slots: 2 * (g + 1) * kSlotStride words (g > 1)
     uint32_t *status;    // per-instance kErr* word
+    const float *src;    // batch: the matrix that the set-up reads (null: D)
     int32_t n;
     int32_t link;
     int32_t exchange;    // kExch* (g > 1)

@@ -945,9 +945,12 @@ __device__ void batch_instance(const Instance &I, int g, int w, uint8_t *smem, C
     for (int li = threadIdx.x; li < own_cap; li += B) L.cache[li] = kEmptyRow;
     __syncthreads();
     uint32_t bad = 0;
+    // A batch that keeps its input is read here from where it lies: a copy
+    // beforehand would pass over all matrices twice more.
+    const float *from = I.src ? I.src : I.D;
     for (int lq = 0; lq < own_ch; ++lq) {
         const int R = chunk_of(lq, g, w);
-        setup_block<B>(I.D, I.D, n, R, R, (n + 63) >> 6, L.tile, bad, [&](int r, uint64_t v) {
+        setup_block<B>(from, I.D, n, R, R, (n + 63) >> 6, L.tile, bad, [&](int r, uint64_t v) {
             L.cache[lq * 64 + r] = v == kEmpty ? kEmptyRow : v;
         });
     }

@@ -284,6 +284,7 @@ bool admit(hac_server *s) {
             E.inst.n = J.n;
             E.inst.link = J.link;
             E.inst.exchange = 0;
+            E.inst.src = nullptr;
             E.inst.flags = J.lazy ? hac::kFlagLazy : 0;
             E.src = src;
             E.ld = ld;
