@@ -35,6 +35,7 @@ constexpr uint32_t kRingCap = 16384;       // entries; >= max_jobs * largest gro
 constexpr int kMaxJobs = 4096;
 constexpr int kMaxGroup = 64;
 constexpr int kGroupN = 2048;              // jobs above this size run on a group
+constexpr int kQuickN = 512;               // the same while the server has workgroups to spare (quick_group)
 constexpr int kPolicyMaxGroup = 16;        // largest group chosen for latency alone
 constexpr int kLargeN = 32768;             // above this, a job gets kMaxGroup workgroups (as hac_run)
 constexpr int kIdleStopMs = 20;            // stop the kernel after this long with nothing to do
@@ -112,6 +113,7 @@ struct hac_server {
     char *jobwords = nullptr;  // device: per job slot, status | members done | exchange slots
     size_t jobwords_stride = 0;
     int max_group = 1;
+    int members = 0;  // workgroups of all jobs waiting or running
     uint64_t published = 0;
     std::vector<uint64_t> ring_owner;  // (id << 32 | seq) of each ring slot's job, 0 = none
     char *dev = nullptr;               // device: ServeDev | Control
@@ -166,6 +168,18 @@ int group_for(int n, size_t lds_cap) {
     if (n > kGroupN) g = n > kLargeN ? kMaxGroup : std::min(kPolicyMaxGroup, pow2_ceil(n / kGroupN));
     while (g < kMaxGroup && hac::lds_bytes(n, hac::own_rows(n, g), true) > lds_cap) g <<= 1;
     return g;
+}
+
+// The same while the workgroups of all jobs held, this one's too, have a compute
+// unit each: a merge step of a group is its exchange and then its share of the
+// rows, so that a lone job ends sooner on a workgroup per kQuickN items (n = 3709,
+// average linkage: 45 ms on 2 workgroups, 26 on 4, 21 on 8, 20 on 16; n = 2000: 16.8
+// on 1, 10.9 on 4, 10.1 on 8; a burst of 48 jobs of 256 to 4096 items 51.2, 34.9, 28.4
+// and 32.1 ms with a workgroup per 2048, 1024, 512 and 256).  A server with more to
+// do than that keeps group_for's, which take less of its workgroups' time.
+int quick_group(int n, size_t lds_cap) {
+    const int g = group_for(n, lds_cap);
+    return n > kQuickN ? std::max(g, std::min(kPolicyMaxGroup, pow2_ceil(n / kQuickN))) : g;
 }
 
 size_t page_bytes(const hac_server *s) {
@@ -334,6 +348,7 @@ bool collect(hac_server *s) {
         s->recs_alloc.release(J.rec_off, J.lay.rec_bytes);
         if (J.staged) s->stage_alloc.release(J.stage_off, J.lay.stage_bytes);
         s->in_use -= J.lay.bytes;
+        s->members -= J.g;
         J.state = JobState::kDone;
         s->completed++;
         s->running[q] = s->running.back();
@@ -482,7 +497,7 @@ int hac_server_create(hac_ctx *ctx, size_t hbm_budget_bytes, int32_t max_jobs, i
     s->stage_bytes = std::min(hbm_budget_bytes, std::max((size_t)1 << 30, align_up((size_t)max_n * max_n * 4, kAlign)));
     // Per job slot: status, members done, and exchange slots for the largest
     // group any job can get; zero now, and left zero by every job.
-    for (int n = 2; n <= max_n; ++n) s->max_group = std::max(s->max_group, group_for(n, s->info.lds_max));
+    for (int n = 2; n <= max_n; ++n) s->max_group = std::max(s->max_group, quick_group(n, s->info.lds_max));
     s->jobwords_stride =
         align_up(kAlign + (s->max_group > 1 ? (size_t)2 * (s->max_group + 1) * hac::kSlotStride * 8 : 0), 4096);
     bool ok = hipMalloc(reinterpret_cast<void **>(&s->dev), s->dev_bytes) == hipSuccess &&
@@ -549,7 +564,9 @@ int hac_submit(hac_server *s, const float *host_dist, int64_t ld, int32_t n, int
     }
     if (s->failed != HAC_OK) return s->failed;
     if (s->quit) return sfail(s, HAC_EINVAL, "server is shutting down");
-    const int g = group_for(n, s->info.lds_max);
+    int g = group_for(n, s->info.lds_max);
+    const int quick = quick_group(n, s->info.lds_max);
+    if (s->members + quick <= s->grid) g = quick;
     if (hac::lds_bytes(n, hac::own_rows(n, g), true) > s->lds || g > s->grid)
         return sfail(s, HAC_EINVAL, "n=%d does not fit the server's workgroups", n);
     const JobLayout lay = job_layout(n);
@@ -583,6 +600,7 @@ int hac_submit(hac_server *s, const float *host_dist, int64_t ld, int32_t n, int
         return HAC_OK;
     }
     J.state = JobState::kWaiting;
+    s->members += g;
     s->waiting.push_back(id);
     s->cv.notify_all();
     return HAC_OK;
