@@ -1,4 +1,5 @@
-// Round engine: single and complete linkage by rounds of merges.
+// Round engine: single and complete linkage by rounds of merges, in place; for
+// n > 32768, where a row no longer fits one workgroup (below, hac_contract.hip).
 //
 // The merge list is the one of Section 4 (steps 1-4): n-1 times, merge the
 // pair of live clusters with the lexicographically smallest key
