@@ -223,7 +223,8 @@ def config_lines(torch, hac, ctx, cpu):
             kms, ims, wall, st = run_timed(ctx, src, link, 5, out)
             got = np.frombuffer(out.cpu().numpy().tobytes(), dtype=hac.MERGE_DTYPE)
             line = {"workload": name, "n": n, "linkage": link, "seed": seed, "gpu_ms": wall, "kernel_ms": kms,
-                    "setup_ms": ims, "engine": "rounds" if st["rounds"] else "one merge per step",
+                    "setup_ms": ims, "engine": "rounds" if st["rounds"] else "ordered rounds" if link in ("average", "weighted", "ward")
+                    else "one merge per step",
                     "rounds": st["rounds"], "handed_over": bool(st["handed_over"])}
             if cpu:
                 t0 = time.perf_counter()

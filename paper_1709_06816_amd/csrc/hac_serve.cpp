@@ -114,6 +114,7 @@ struct hac_server {
     size_t jobwords_stride = 0;
     int max_group = 1;
     int members = 0;  // workgroups of all jobs waiting or running
+    bool quick = true;  // exchange slots for quick_group's groups
     uint64_t published = 0;
     std::vector<uint64_t> ring_owner;  // (id << 32 | seq) of each ring slot's job, 0 = none
     char *dev = nullptr;               // device: ServeDev | Control
@@ -497,11 +498,20 @@ int hac_server_create(hac_ctx *ctx, size_t hbm_budget_bytes, int32_t max_jobs, i
     s->stage_bytes = std::min(hbm_budget_bytes, std::max((size_t)1 << 30, align_up((size_t)max_n * max_n * 4, kAlign)));
     // Per job slot: status, members done, and exchange slots for the largest
     // group any job can get; zero now, and left zero by every job.
-    for (int n = 2; n <= max_n; ++n) s->max_group = std::max(s->max_group, quick_group(n, s->info.lds_max));
-    s->jobwords_stride =
-        align_up(kAlign + (s->max_group > 1 ? (size_t)2 * (s->max_group + 1) * hac::kSlotStride * 8 : 0), 4096);
+    // Without memory for quick_group's, jobs get group_for's.
+    for (const bool quick : {true, false}) {
+        s->quick = quick;
+        s->max_group = 1;
+        for (int n = 2; n <= max_n; ++n)
+            s->max_group = std::max(s->max_group, quick ? quick_group(n, s->info.lds_max) : group_for(n, s->info.lds_max));
+        s->jobwords_stride =
+            align_up(kAlign + (s->max_group > 1 ? (size_t)2 * (s->max_group + 1) * hac::kSlotStride * 8 : 0), 4096);
+        if (hipMalloc(reinterpret_cast<void **>(&s->jobwords), s->jobwords_stride * max_jobs) == hipSuccess) break;
+        (void)hipGetLastError();
+        s->jobwords = nullptr;
+    }
     bool ok = hipMalloc(reinterpret_cast<void **>(&s->dev), s->dev_bytes) == hipSuccess &&
-              hipMalloc(reinterpret_cast<void **>(&s->jobwords), s->jobwords_stride * max_jobs) == hipSuccess &&
+              s->jobwords &&
               hipMemset(s->jobwords, 0, s->jobwords_stride * max_jobs) == hipSuccess &&
               hipDeviceSynchronize() == hipSuccess &&
               hipHostMalloc(reinterpret_cast<void **>(&s->hostmem), host_bytes,
@@ -566,7 +576,7 @@ int hac_submit(hac_server *s, const float *host_dist, int64_t ld, int32_t n, int
     if (s->quit) return sfail(s, HAC_EINVAL, "server is shutting down");
     int g = group_for(n, s->info.lds_max);
     const int quick = quick_group(n, s->info.lds_max);
-    if (s->members + quick <= s->grid) g = quick;
+    if (s->quick && s->members + quick <= s->grid) g = quick;
     if (hac::lds_bytes(n, hac::own_rows(n, g), true) > s->lds || g > s->grid)
         return sfail(s, HAC_EINVAL, "n=%d does not fit the server's workgroups", n);
     const JobLayout lay = job_layout(n);
