@@ -200,8 +200,11 @@ struct Clock {
 
 template <int link>
 __global__ __launch_bounds__(B) void k_contract(Args A) {
-    __shared__ uint64_t s_key[W];  // per wave: a row's smallest entry
-    __shared__ uint32_t s_cnt[W];
+    // Per wave: its part of a row's smallest entry.  Two sets, taken in turn: a
+    // row's words are read after its one barrier, when other waves may already
+    // be writing the next row's (the first pass has no second barrier per row).
+    __shared__ uint64_t s_key[2][W];
+    __shared__ uint32_t s_cnt[2][W];
     __shared__ uint64_t s_k1;
     __shared__ unsigned long long s_prof[kPhases];
     constexpr bool kCount = link == HAC_SINGLE;
@@ -430,16 +433,16 @@ __global__ __launch_bounds__(B) void k_contract(Args A) {
                     (uint32_t)wave_sum(low.o == (uint32_t)(best >> 32) ? (unsigned long long)low.cnt : 0ull);
                 __syncthreads();
                 if (lane == 0) {
-                    s_key[wv] = best;
-                    s_cnt[wv] = ties;
+                    s_key[0][wv] = best;
+                    s_cnt[0][wv] = ties;
                 }
                 __syncthreads();
                 if (tid == 0) {
                     uint64_t b = kNone;
-                    for (int q = 0; q < W; ++q) b = umin64(b, s_key[q]);
+                    for (int q = 0; q < W; ++q) b = umin64(b, s_key[0][q]);
                     uint32_t t = 0;
                     for (int q = 0; q < W; ++q)
-                        if ((uint32_t)(s_key[q] >> 32) == (uint32_t)(b >> 32)) t += s_cnt[q];
+                        if ((uint32_t)(s_key[0][q] >> 32) == (uint32_t)(b >> 32)) t += s_cnt[0][q];
                     st64(A.part + unit, b);
                     st32(A.pcnt + unit, t);
                     if (at == 0) {
@@ -676,18 +679,19 @@ __global__ __launch_bounds__(B) void k_contract(Args A) {
                 if (kCount)
                     ties = (uint32_t)wave_sum(low.o == (uint32_t)(best >> 32) ? (unsigned long long)low.cnt : 0ull);
                 if (lane == 0) {
-                    s_key[wv] = best;
-                    if (kCount) s_cnt[wv] = ties;
+                    s_key[it & 1][wv] = best;
+                    if (kCount) s_cnt[it & 1][wv] = ties;
                 }
             }
             __syncthreads();
             if (valid && t == 0) {
                 uint64_t best = kNone;
-                for (int q = 0; q < T / 64; ++q) best = umin64(best, s_key[wv + q]);
+                const uint64_t *keys = s_key[it & 1] + wv;
+                for (int q = 0; q < T / 64; ++q) best = umin64(best, keys[q]);
                 if (kCount) {
                     uint32_t ties = 0;
                     for (int q = 0; q < T / 64; ++q)
-                        if ((uint32_t)(s_key[wv + q] >> 32) == (uint32_t)(best >> 32)) ties += s_cnt[wv + q];
+                        if ((uint32_t)(keys[q] >> 32) == (uint32_t)(best >> 32)) ties += s_cnt[it & 1][wv + q];
                     st32(A.ns[out] + r, (uint32_t)best);
                     st32(A.ties[out] + r, ties);
                 } else {
