@@ -708,8 +708,10 @@ __global__ __launch_bounds__(B) void k_contract(Args A) {
         par = out;
         aligned = shorter;
         first = false;
-        if (kCount)
+        if (kCount) {
             for (int q = tid; q < kWords; q += B) dead[q] = 0;
+            __syncthreads();  // every wave reads the whole mask next
+        }
         }
         // Fewer workgroups as the rows get fewer: the barriers cost less.
         const int keep = m > 4096 ? G : min(G, m > 1024 ? 128 : m > 256 ? 64 : m > 64 ? 16 : 4);
