@@ -33,6 +33,7 @@ constexpr int64_t kDefaultTimeoutMs = 10000;
 // 1.65; single n=150 0.43 / 0.41 (tied input), n=300 0.59 / 0.85.
 constexpr int kSmallComplete = 144;     // complete linkage: the small-instance kernel up to this n
 constexpr int kRoundsMinComplete = 64, kRoundsMinSingle = 200;
+constexpr int kInplaceMinN = 8192;      // complete linkage: above, rounds of few pairs go on in place (hac_contract.hip)
 constexpr int kOrderMinN = 192;         // the same for the ordered rounds of the averaging linkages (n=200: 0.57 ms
                                         // against 0.65 one merge per step, n=100: 0.36 against 0.29)
 
@@ -778,10 +779,15 @@ int run_rounds(hac_ctx *c, float *dist, int32_t n, int32_t linkage, hac_merge *o
     const size_t st_off = ctl_bytes, st_bytes = kAlign;
     const size_t rk_off = st_off + st_bytes, rk_bytes = align_up((size_t)n * 8, kAlign);
     const size_t ro_off = rk_off + rk_bytes;
-    const hac::RoundsLayout Lr = hac::rounds_layout(n, G);
+    // Complete linkage above kInplaceMinN: the in-place round engine is queued
+    // behind the contraction engine, which leaves it runs of few pairs a round.
+    const bool inplace_next = contract && linkage == HAC_COMPLETE && n > kInplaceMinN;
+    int Gr = c->cus * hac::rounds_occupancy();
+    if (c->opt_wgs > 0) Gr = std::min(Gr, (int)c->opt_wgs);
     const hac::ContractLayout Lc = hac::contract_layout(n);
+    const hac::RoundsLayout Lr = contract ? hac::contract_rounds_layout(n, Gr) : hac::rounds_layout(n, Gr);
     const size_t zero_bytes = contract ? Lc.zero_bytes : Lr.zero_bytes;
-    const size_t sl_off = ro_off + (contract ? Lc.bytes : Lr.bytes);
+    const size_t sl_off = ro_off + (contract && !inplace_next ? Lc.bytes : Lr.bytes);
     const size_t sl_bytes = (handover && g > 1) ? (size_t)2 * (g + 1) * hac::kSlotStride * 8 : 0;
     rc = ensure_dev(c, &c->ws, &c->ws_cap, sl_off + sl_bytes, "workspace");
     if (rc) return rc;
@@ -814,6 +820,7 @@ int run_rounds(hac_ctx *c, float *dist, int32_t n, int32_t linkage, hac_merge *o
     HIP_TRY(c, hipEventRecord(c->ev[0], s));
     HIP_TRY(c, hac::launch_zero(ws, (st_off + st_bytes) / 4, s));
     HIP_TRY(c, hac::launch_zero(ws + ro_off, zero_bytes / 4, s));
+    if (inplace_next) HIP_TRY(c, hac::launch_zero(ws + ro_off + Lr.ctl, sizeof(hac::RoundsCtl) / 4, s));
     if (sl_bytes) HIP_TRY(c, hac::launch_zero(ws + sl_off, sl_bytes / 4, s));
     HIP_TRY(c, hac::launch_setup(inst, dist, s));
     HIP_TRY(c, hipEventRecord(c->ev[1], s));
@@ -821,9 +828,12 @@ int run_rounds(hac_ctx *c, float *dist, int32_t n, int32_t linkage, hac_merge *o
                        (c->opt_stall ? hac::kFlagStall : 0);
     hac::Control *ctl = reinterpret_cast<hac::Control *>(ws);
     hipError_t e = contract ? hac::launch_contract(D, n, linkage, inst.status, ctl, ws + ro_off, G, timeout_ticks(c),
-                                                   rflags, s)
-                            : hac::launch_rounds(D, n, linkage, inst.status, ctl, ws + ro_off, G, timeout_ticks(c),
-                                                 rflags, s);
+                                                   rflags | (inplace_next ? hac::kFlagInplaceNext : 0), s)
+                            : hac::launch_rounds(D, n, linkage, inst.status, ctl, ws + ro_off, Lr, G,
+                                                 timeout_ticks(c), rflags, s);
+    if (e == hipSuccess && inplace_next)
+        e = hac::launch_rounds(D, n, linkage, inst.status, ctl, ws + ro_off, Lr, Gr, timeout_ticks(c),
+                               rflags | hac::kFlagAfterRounds, s);
     if (e != hipSuccess) return hip_fail(c, e, "round kernel launch");
     HIP_TRY(c, hipEventRecord(c->ev[3], s));
     if (handover) {
@@ -835,7 +845,7 @@ int run_rounds(hac_ctx *c, float *dist, int32_t n, int32_t linkage, hac_merge *o
         seq.exchange = (int32_t)c->opt_exchange;
         seq.flags = seq_flags | hac::kFlagAfterRounds;
         e = hac::launch_merge(seq, g, block, ctl, timeout_ticks(c), s,
-                              contract ? hac::contract_resume(n, ws + ro_off) : hac::rounds_resume(n, G, ws + ro_off));
+                              contract ? hac::contract_resume(n, ws + ro_off) : hac::rounds_resume(Lr, ws + ro_off));
         if (e != hipSuccess) return hip_fail(c, e, "merge kernel launch");
     }
     e = hac::launch_rank(n, dev_out, inst.status, ctl, ws + ro_off + (contract ? Lc.rec : Lr.rec),

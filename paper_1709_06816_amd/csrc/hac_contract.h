@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "hac_engine.h"
+#include "hac_rounds.h"
 
 namespace hac {
 
@@ -33,9 +34,16 @@ int contract_occupancy(int link);
 // The rounds of HAC_SINGLE or HAC_COMPLETE on G co-resident workgroups, from
 // the symmetric matrix written by the set-up kernel.  Records (claim order,
 // with sort keys) stay in the workspace until launch_rank writes them in merge
-// order.  Hands over as launch_rounds does (kHandover, contract_resume).
+// order.  Hands over as launch_rounds does (kHandover, contract_resume), and with
+// kFlagInplaceNext in `flags` (complete linkage) leaves the rest to a launch_rounds
+// queued behind it on the layout contract_rounds_layout (kInplace in `status`) when
+// rounds have too few pairs to stream the matrix for them.
 hipError_t launch_contract(float *D, int n, int link, uint32_t *status, Control *ctl, void *ws, int G,
                            uint64_t timeout_ticks, int flags, hipStream_t stream);
 Resume contract_resume(int n, void *ws);
+// Workspace of that launch_rounds, on the same base: its own words follow the
+// contraction engine's (ctl: to be cleared, sizeof(RoundsCtl)); records, keys, live
+// mask, sizes and hand-over state are the same, so that contract_resume serves both.
+RoundsLayout contract_rounds_layout(int n, int G);
 
 }  // namespace hac

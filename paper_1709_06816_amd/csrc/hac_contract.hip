@@ -59,6 +59,19 @@ constexpr int kHandoverLeft = 96;            // the last merges are made here: t
 
 constexpr int kWideMin = 4096;
 constexpr int kInplaceMin = 1024;            // smaller matrices are contracted every round
+// Complete linkage leaves the rest to the in-place round engine when two rounds
+// running, or the first, have fewer pairs than this.  With p pairs in every round that is left, m
+// clusters cost m / p rounds here of 0.63e-6 m^2 us on average (a third of the
+// first one's 8 m^2 bytes at 4.2 TB/s), there of 40 us more than here for the
+// barriers and about 3.5e-5 n us a pair (column stores, rescans of full rows).
+// Points on C lines, which merge about 2 C pairs a round; streamed / in place from the
+// start / this rule: n = 32768, C = 16: 650 / 82 / 81 ms, C = 150: 78 / 37 / 38, C = 400:
+// 34 / 32 / 32, C = 1000: 17 / 26 / 17; n = 16000, C = 16: 91 / 33 / 33, C = 250: 7.9 /
+// 8.6 / 7.9.  Up to 8192 items rounds here are never the dearer ones (n = 8192, C = 16:
+// 15.3 / 15.4, C = 40: 6.7 / 9.1), and no engine is queued behind.
+__device__ __forceinline__ bool cheaper_in_place(int np, int m, int n) {
+    return (float)np * (3.5e-5f * (float)n) < 0.63e-6f * (float)m * (float)m - 40.0f;
+}
 static_assert(KE * B == kMaxM && KE == 4 * U, "a row takes one workgroup, four chunks");
 
 // LDS (dynamic), byte offsets.  The row area holds the rows on their way;
@@ -247,6 +260,8 @@ __global__ __launch_bounds__(B) void k_contract(Args A) {
     };
     uint64_t window = 0;  // merges of the last 8 rounds, at most 255 each, a byte each
     int recent = 0;       // their sum
+    int sparse = 0;       // complete: rounds running that would have been cheaper in place
+    uint32_t leave = 0;   // the kernel that makes the remaining merges (kHandover, kInplace)
     const bool may_hand_over = !(A.flags & kFlagNoHandover);
     bool aligned = false;  // the rows' storage as it is now (row_at)
     bool first = true, stall = (A.flags & kFlagStall) && w == 0;
@@ -348,6 +363,13 @@ __global__ __launch_bounds__(B) void k_contract(Args A) {
                     __hip_atomic_store(&A.cc->abort, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
                 }
                 return;
+            }
+        }
+        if (link == HAC_COMPLETE && (A.flags & kFlagInplaceNext) && !first) {
+            sparse = cheaper_in_place(np, m, n) ? sparse + 1 : 0;
+            if (sparse == 2 || (sparse && round == 0)) {  // nothing of this round has been applied
+                leave = kInplace;
+                break;
             }
         }
         // Single linkage with few pairs: their rows and columns in place, the
@@ -718,40 +740,44 @@ __global__ __launch_bounds__(B) void k_contract(Args A) {
         if (w >= keep) return;
         G = keep;
         if (may_hand_over && round >= kWindow && n - merges > kHandoverLeft && recent < kWindow * kMinPerRound) {
-            __syncthreads();
-            // Rows back to their columns' slots for the one-merge-per-step kernel.
-            for (int q = w; q < m; q += G) {
-                if ((dead[q >> 6] >> (q & 63)) & 1ull) continue;
-                const int s = A.slot[par][q];
-                const float *from = row_at(D, n, s, aligned);
-                float *p = D + (size_t)s * n;
-                for (int c = tid; c < m; c += B) row[c] = __float_as_uint(from[c]);
-                __syncthreads();
-                for (int c = tid; c < m; c += B) p[A.slot[par][c]] = __uint_as_float(row[c]);
-                __syncthreads();
-            }
-            __syncthreads();
-            for (int c = w * B + tid; c < m; c += G * B)
-                if (!((dead[c >> 6] >> (c & 63)) & 1ull)) A.hsize[A.slot[par][c]] = A.size[par][c];
-            if (w == 0) {
-                uint32_t *bits = lds<uint32_t>(oRow);
-                const int words = (n + 31) >> 5;
-                for (int q = tid; q < words; q += B) bits[q] = 0;
-                __syncthreads();
-                for (int c = tid; c < m; c += B) {
-                    if ((dead[c >> 6] >> (c & 63)) & 1ull) continue;
-                    const int s = A.slot[par][c];
-                    atomicOr(&bits[s >> 5], 1u << (s & 31));
-                }
-                __syncthreads();
-                for (int q = tid; q < words; q += B) A.live[q] = bits[q];
-                if (tid == 0) {
-                    A.cc->merges = (uint32_t)merges;
-                    A.cc->round = (uint32_t)round;
-                    atomicOr(A.status, kHandover);
-                }
-            }
+            leave = kHandover;
             break;
+        }
+    }
+    if (leave) {
+        __syncthreads();
+        // Rows back to their columns' slots for the kernel that goes on (they are
+        // still there before the first contraction).
+        for (int q = w; q < m && m < n; q += G) {
+            if ((dead[q >> 6] >> (q & 63)) & 1ull) continue;
+            const int s = A.slot[par][q];
+            const float *from = row_at(D, n, s, aligned);
+            float *p = D + (size_t)s * n;
+            for (int c = tid; c < m; c += B) row[c] = __float_as_uint(from[c]);
+            __syncthreads();
+            for (int c = tid; c < m; c += B) p[A.slot[par][c]] = __uint_as_float(row[c]);
+            __syncthreads();
+        }
+        __syncthreads();
+        for (int c = w * B + tid; c < m; c += G * B)
+            if (!((dead[c >> 6] >> (c & 63)) & 1ull)) A.hsize[A.slot[par][c]] = A.size[par][c];
+        if (w == 0) {
+            uint32_t *bits = lds<uint32_t>(oRow);
+            const int words = (n + 31) >> 5;
+            for (int q = tid; q < words; q += B) bits[q] = 0;
+            __syncthreads();
+            for (int c = tid; c < m; c += B) {
+                if ((dead[c >> 6] >> (c & 63)) & 1ull) continue;
+                const int s = A.slot[par][c];
+                atomicOr(&bits[s >> 5], 1u << (s & 31));
+            }
+            __syncthreads();
+            for (int q = tid; q < words; q += B) A.live[q] = bits[q];
+            if (tid == 0) {
+                A.cc->merges = (uint32_t)merges;
+                A.cc->round = (uint32_t)round;
+                atomicOr(A.status, leave);
+            }
         }
     }
     if (w == 0 && tid == 0) {
@@ -842,6 +868,17 @@ hipError_t launch_contract(float *D, int n, int link, uint32_t *status, Control 
     a.flags = flags;
     void *args[] = {&a};
     return hipLaunchCooperativeKernel(contract_kernel(link), dim3(G), dim3(B), args, kLdsBytes, stream);
+}
+
+RoundsLayout contract_rounds_layout(int n, int G) {
+    const ContractLayout Lc = contract_layout(n);
+    RoundsLayout L = rounds_layout(n, G, Lc.bytes);
+    L.rec = Lc.rec;
+    L.key = Lc.key;
+    L.live = Lc.live;
+    L.size = Lc.hsize;
+    L.state = Lc.ctl + offsetof(ContractCtl, merges);
+    return L;
 }
 
 Resume contract_resume(int n, void *ws) {

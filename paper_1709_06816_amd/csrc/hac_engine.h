@@ -23,6 +23,8 @@ enum : uint32_t {
     kErrInternal = 4u,  // no live pair found although >= 2 clusters remain
     kHandover = 8u,     // not an error: the round engine left the instance to the
                         // one-merge-per-step kernel queued behind it
+    kInplace = 16u,     // not an error: the contraction engine left it to the in-place
+                        // round engine queued behind it
 };
 
 // Phases timed by each workgroup (device wall clock).
@@ -71,13 +73,15 @@ enum : int32_t {
     kFlagScan = 2,     // no cached row minima: every merge rescans every live row (Section 5.3 step 1)
     kFlagDefer = 4,    // rows whose partner merged keep a lower bound and are rescanned while
                        // their workgroup waits in the next exchange (single instance, g > 1)
-    kFlagAfterRounds = 8,  // k_run queued behind the round engine: runs only on kHandover
+    kFlagAfterRounds = 8,  // k_run queued behind the round engine: runs only on kHandover; k_rounds
+                           // queued behind the contraction engine: runs only on kInplace
     kFlagNoHandover = 16,  // round engine: never hand over, rounds to the end (HAC_OPT_ROUNDS = 2)
     kFlagStall = 32,       // failure test: workgroup 0 never publishes, so the other
                            // workgroups' bounded waits expire (HAC_OPT_INJECT_STALL)
     kFlagLazy = 64,        // lazy mirror (batch and serving kernels): the update writes row i
                            // only, and a pair's current value is read from the one of its two
                            // rows written last (write steps in LDS); needs lds_bytes(.., true)
+    kFlagInplaceNext = 128,  // contraction engine: k_rounds is queued behind it
 };
 
 // State left by the round engine when it hands an instance over part-way

@@ -18,8 +18,7 @@ struct RoundsCtl {
     uint32_t abort;           // set by a workgroup that gives up
     uint32_t pairs;           // pairs claimed in the current round
     uint32_t resc;            // rows queued for a rescan in the current round
-    uint32_t merges;          // at a hand-over: merges done (read as Resume::state[0])
-    uint32_t round;           //   and rounds run (Resume::state[1])
+    uint32_t state[2];        // at a hand-over: merges done, rounds run (Resume::state)
     uint32_t pad[2];
 };
 
@@ -28,9 +27,12 @@ struct RoundsCtl {
 struct RoundsLayout {
     size_t ctl, rank;    // cleared before a launch: zero_bytes from the start
     size_t zero_bytes;
-    size_t rk, cnt, size, role, resc, pairs, k1, rec, key, live, bytes;
+    size_t rk, cnt, size, role, resc, pairs, k1, rec, key, live;
+    size_t state;        // hand-over: merges done, rounds run (two words)
+    size_t bytes;        // end
 };
-RoundsLayout rounds_layout(int n, int G);
+// `at`: where its words start (behind another engine's on the same base).
+RoundsLayout rounds_layout(int n, int G, size_t at = 0);
 
 // Workgroups of the round kernel that fit on one CU.
 int rounds_occupancy();
@@ -44,16 +46,18 @@ int rounds_occupancy();
 // (kHandover in `status`, state in the workspace: rounds_resume) unless
 // `flags` has kFlagNoHandover: a k_run launch with kFlagAfterRounds queued
 // behind it then does them.
-// `ws` is the workspace laid out by rounds_layout (its control block zeroed
+// With kFlagAfterRounds it runs only on kInplace in `status` and resumes from
+// the live mask, sizes and state in the workspace, appending to its records.
+// `ws` is the workspace laid out by `Lo` (its control block zeroed
 // beforehand).  link is HAC_SINGLE or HAC_COMPLETE.
 // Errors and statistics go to `ctl` (rescans, rescan_elems, update_elems,
 // rounds; with kFlagProfile in `flags`, per-workgroup phase times: [0] first
 // rescans, [1] grid barriers, [2] updates, [3] rescans, [4] pair detection).
-hipError_t launch_rounds(float *D, int n, int link, uint32_t *status, Control *ctl, void *ws, int G,
-                         uint64_t timeout_ticks, int flags, hipStream_t stream);
+hipError_t launch_rounds(float *D, int n, int link, uint32_t *status, Control *ctl, void *ws, const RoundsLayout &Lo,
+                         int G, uint64_t timeout_ticks, int flags, hipStream_t stream);
 
 // Hand-over state inside a round-engine workspace (for launch_merge).
-Resume rounds_resume(int n, int G, void *ws);
+Resume rounds_resume(const RoundsLayout &Lo, void *ws);
 
 // The n-1 records `rec` (16 bytes each, device) with sort keys `key` written to
 // `out` in key order; `rank`: n words, zero.  Nothing is written if the launch

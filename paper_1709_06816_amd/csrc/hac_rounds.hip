@@ -1,5 +1,6 @@
 // Round engine: single and complete linkage by rounds of merges, in place; for
-// n > 32768, where a row no longer fits one workgroup (below, hac_contract.hip).
+// n > 32768, where a row no longer fits one workgroup (below, hac_contract.hip),
+// and for the rest of a complete linkage run there whose rounds have few pairs.
 //
 // The merge list is the one of Section 4 (steps 1-4): n-1 times, merge the
 // pair of live clusters with the lexicographically smallest key
@@ -197,6 +198,7 @@ struct Views {
     int4 *rec;         // n-1 records in claim order
     uint64_t *key;     // their sort keys ord(h):32 | i:16 | round:16
     uint32_t *live;    // live mask left at a hand-over
+    uint32_t *state;   //   and merges done, rounds run
 };
 
 __device__ Views views(char *ws, const RoundsLayout &Lo) {
@@ -212,6 +214,7 @@ __device__ Views views(char *ws, const RoundsLayout &Lo) {
     v.rec = reinterpret_cast<int4 *>(ws + Lo.rec);
     v.key = reinterpret_cast<uint64_t *>(ws + Lo.key);
     v.live = reinterpret_cast<uint32_t *>(ws + Lo.live);
+    v.state = reinterpret_cast<uint32_t *>(ws + Lo.state);
     return v;
 }
 
@@ -254,16 +257,21 @@ __global__ __launch_bounds__(kRoundsBlock) void k_rounds(float *D, int n, int li
     const int w = (int)blockIdx.x, tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6;
     const int gw = w * W + wv, NW = (int)G * W;
     unsigned long long st_upd = 0, st_resc = 0, st_rows = 0;
-    // The set-up kernel has finished: its verdict is final.
-    if (__hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & kErrInput) return;
+    // The set-up kernel (and an engine in front of this one) has finished: its
+    // verdict is final.
+    const uint32_t st0 = __hip_atomic_load(status, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const bool resumed = (flags & kFlagAfterRounds) != 0;
+    if ((st0 & kErrInput) || (resumed && !(st0 & kInplace))) return;
 
     const int words = (n + 31) >> 5;
     for (int q = tid; q < words; q += B) {
         const int rem = n - q * 32;
-        s_live[q] = rem >= 32 ? 0xFFFFFFFFu : ((1u << rem) - 1u);
+        s_live[q] = resumed ? V.live[q] : rem >= 32 ? 0xFFFFFFFFu : ((1u << rem) - 1u);
     }
+    int merges = resumed ? (int)V.state[0] : 0, round = resumed ? (int)V.state[1] : 0;
+    const int round0 = round;
     for (int k = w * B + tid; k < n; k += (int)G * B) {
-        V.size[k] = 1;
+        if (!resumed) V.size[k] = 1;
         V.role[k] = 0;
         V.rk[k] = kNone;
         V.cw[k] = kNoCount;
@@ -274,6 +282,7 @@ __global__ __launch_bounds__(kRoundsBlock) void k_rounds(float *D, int n, int li
     const int nseg = (n + kSeg - 1) / kSeg;
     // First cache entries: every row's minimum over the whole row.
     for (int t = gw; t < n * nseg; t += NW) {
+        if (!live_at(t / nseg)) continue;
         rescan_segment(D, n, t / nseg, t % nseg, V.rk, V.cw, st_resc);
         st_rows += (t % nseg) == 0;
     }
@@ -286,9 +295,8 @@ __global__ __launch_bounds__(kRoundsBlock) void k_rounds(float *D, int n, int li
     const bool may_hand_over = !(flags & kFlagNoHandover);
     int window[kWindow] = {0};  // merges of the last kWindow rounds
     const int nblocks = (n + 63) >> 6;
-    int merges = 0, round = 0;
     while (merges < n - 1) {
-        if (may_hand_over && round >= kWindow) {
+        if (may_hand_over && round - round0 >= kWindow) {
             int recent = 0;
 #pragma unroll
             for (int t = 0; t < kWindow; ++t) recent += window[t];
@@ -297,8 +305,8 @@ __global__ __launch_bounds__(kRoundsBlock) void k_rounds(float *D, int n, int li
                 if (w == 0) {
                     for (int q = tid; q < words; q += B) V.live[q] = s_live[q];
                     if (tid == 0) {
-                        V.rc->merges = (uint32_t)merges;
-                        V.rc->round = (uint32_t)round;
+                        V.state[0] = (uint32_t)merges;
+                        V.state[1] = (uint32_t)round;
                         atomicOr(status, kHandover);
                     }
                 }
@@ -554,13 +562,14 @@ __global__ __launch_bounds__(256) void k_rank_place(const int4 *__restrict__ rec
 
 }  // namespace
 
-RoundsLayout rounds_layout(int n, int G) {
+RoundsLayout rounds_layout(int n, int G, size_t at) {
     auto al = [](size_t x) { return (x + 255) / 256 * 256; };
     RoundsLayout L{};
-    size_t off = 0;
+    size_t off = at;
     L.ctl = off;   off += al(sizeof(RoundsCtl));
+    L.state = L.ctl + offsetof(RoundsCtl, state);
     L.rank = off;  off += al((size_t)n * 4);
-    L.zero_bytes = off;
+    L.zero_bytes = off - at;
     L.rk = off;    off += al((size_t)n * 8);
     L.cnt = off;   off += al((size_t)n * 8);
     L.size = off;  off += al((size_t)n * 4);
@@ -585,9 +594,8 @@ int rounds_occupancy() {
     return blocks < 1 ? 1 : blocks;
 }
 
-hipError_t launch_rounds(float *D, int n, int link, uint32_t *status, Control *ctl, void *ws, int G,
-                         uint64_t timeout_ticks, int flags, hipStream_t stream) {
-    const RoundsLayout Lo = rounds_layout(n, G);
+hipError_t launch_rounds(float *D, int n, int link, uint32_t *status, Control *ctl, void *ws, const RoundsLayout &Lo,
+                         int G, uint64_t timeout_ticks, int flags, hipStream_t stream) {
     float *a0 = D;
     int a1 = n;
     int a2 = link;
@@ -614,14 +622,13 @@ hipError_t launch_rank(int n, hac_merge *out, const uint32_t *status, const Cont
     return hipGetLastError();
 }
 
-Resume rounds_resume(int n, int G, void *ws) {
-    const RoundsLayout Lo = rounds_layout(n, G);
+Resume rounds_resume(const RoundsLayout &Lo, void *ws) {
     char *b = static_cast<char *>(ws);
     Resume r;
     r.live = reinterpret_cast<const uint32_t *>(b + Lo.live);
     r.size = reinterpret_cast<const int32_t *>(b + Lo.size);
     r.keys = reinterpret_cast<uint64_t *>(b + Lo.key);
-    r.state = reinterpret_cast<const uint32_t *>(b + Lo.ctl + offsetof(RoundsCtl, merges));
+    r.state = reinterpret_cast<const uint32_t *>(b + Lo.state);
     return r;
 }
 
