@@ -59,6 +59,12 @@ constexpr int kHandoverLeft = 96;            // the last merges are made here: t
 
 constexpr int kWideMin = 4096;
 constexpr int kInplaceMin = 1024;            // smaller matrices are contracted every round
+// Columns per retired column at which single linkage contracts.  A contraction streams
+// the matrix, in between every row carries the retired columns along.  12 / 6 / 4 / 3: points
+// growing in 150 chains, n = 32768, 43.2 / 38.6 / 37.2 / 37.3 ms; mixture of 32 clusters
+// in 3 dimensions 28.0 / 28.1 / 28.7 / 32.0, in 16 dimensions 50.0 / 48.3 / 47.4 / 48.4, and
+// at n = 8192 6.16 / 5.92 / 5.97 / 5.92.
+constexpr int kRetired = 6;
 // Complete linkage leaves the rest to the in-place round engine when two rounds
 // running, or the first, have fewer pairs than this.  With p pairs in every round that is left, m
 // clusters cost m / p rounds here of 0.63e-6 m^2 us on average (a third of the
@@ -373,8 +379,8 @@ __global__ __launch_bounds__(B) void k_contract(Args A) {
             }
         }
         // Single linkage with few pairs: their rows and columns in place, the
-        // retired columns stay until they are a twelfth.
-        const bool inplace = kCount && !first && m > kInplaceMin && (m - mk) * 12 < m && mk > 1;
+        // retired columns stay until they are kRetired of the whole.
+        const bool inplace = kCount && !first && m > kInplaceMin && (m - mk) * kRetired < m && mk > 1;
         // Every workgroup has read the nearest neighbours before one changes, and
         // the joined rows of an update in place are kept.
         if (kCount && (inplace || parts) && !arrive_and_wait(A, arrivals, (uint32_t)G, false)) return;

@@ -1,5 +1,5 @@
 """Single linkage on tied values in the contraction engine, rounds to the end:
-rounds update in place until a twelfth of the columns have retired, then one
+rounds update in place until a share of the columns have retired, then one
 contracts, over and over, so that every contraction starts from a mask of retired
 columns that the next round must find empty.  Against the CPU oracle."""
 import numpy as np
