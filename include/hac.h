@@ -401,7 +401,9 @@ int hac_get_stats(const hac_ctx *ctx, hac_stats *out);
  * workgroups.  A job's merge list is byte-identical to hac_run on the same
  * matrix, whatever else runs beside it.  A host thread of the server drives
  * admission, publication and completion; the kernel stops after a short
- * idle period and is relaunched on demand.
+ * idle period and is relaunched on demand.  While it runs it holds all but a
+ * few compute units: a hac_run of up to 256 items completes beside it, a larger
+ * one (and hac_batch) when it has stopped.
  *
  * hac_server_create -- ctx: a context (its device and HAC_OPT_TIMEOUT_MS are
  *   read at creation; the server keeps no reference; the timeout bounds the

@@ -36,6 +36,12 @@ constexpr int kRoundsMinComplete = 64, kRoundsMinSingle = 200;
 constexpr int kInplaceMinN = 8192;      // complete linkage: above, rounds of few pairs go on in place (hac_contract.hip)
 constexpr int kOrderMinN = 192;         // the same for the ordered rounds of the averaging linkages (n=200: 0.57 ms
                                         // against 0.65 one merge per step, n=100: 0.36 against 0.29)
+// A running serving kernel takes all but one compute unit per XCD for as long as it
+// has jobs.  Beside it launches of a few plain workgroups complete, cooperative ones
+// and larger grids wait until it stops.  Up to this n the one-merge-per-step path
+// has only such launches (n = 256: 0.96 ms beside a server, 257: until it stops), so
+// these calls take it while a serving kernel runs.
+constexpr int kBesideServerN = 256;
 
 size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
 
@@ -760,7 +766,7 @@ int run_rounds(hac_ctx *c, float *dist, int32_t n, int32_t linkage, hac_merge *o
     if (!c->coop) return fail(c, HAC_EDEVICE, "device does not support cooperative launch");
     // On a shrinking matrix where a row fits a workgroup, in place above.
     const bool contract = n <= hac::kContractMaxN && hac::contract_occupancy(linkage) > 0;
-    int G = c->cus * (contract ? 1 : hac::rounds_occupancy());
+    int G = contract ? hac::contract_workgroups(n, c->cus) : c->cus * hac::rounds_occupancy();
     if (c->opt_wgs > 0) G = std::min(G, (int)c->opt_wgs);
     // Automatic mode: the one-merge-per-step kernel is queued behind the
     // round engine and makes the remaining merges if the round engine hands
@@ -1078,13 +1084,14 @@ int run_impl(hac_ctx *c, float *dist, int32_t n, int32_t linkage, hac_merge *out
     if (!noalloc && !(flags & HAC_MODE_SCAN) && n <= (linkage == HAC_COMPLETE ? kSmallComplete : hac::kSmallMaxN) && c->opt_rounds == 1 && c->opt_defer == 1 &&
         !c->opt_wgs && !c->opt_single_n && !c->opt_block && !c->opt_profile)
         return run_small(c, dist, n, linkage, out, flags, s);
+    // Rounds unless a serving kernel could hold the call up (kBesideServerN).
+    const bool rounds = c->opt_rounds == 1 && !(n <= kBesideServerN && hac::serving_cus(c->device) > 0);
     if (!noalloc && !(flags & HAC_MODE_SCAN) && (linkage == HAC_SINGLE || linkage == HAC_COMPLETE) &&
-        (c->opt_rounds == 2 ||
-         (c->opt_rounds == 1 && n >= (linkage == HAC_SINGLE ? kRoundsMinSingle : kRoundsMinComplete))))
+        (c->opt_rounds == 2 || (rounds && n >= (linkage == HAC_SINGLE ? kRoundsMinSingle : kRoundsMinComplete))))
         return run_rounds(c, dist, n, linkage, out, flags, s);
     if (!noalloc && (flags & HAC_MODE_SCAN)) return run_scan(c, dist, n, linkage, out, flags, s);
     if (!noalloc && (linkage == HAC_AVERAGE || linkage == HAC_WEIGHTED || linkage == HAC_WARD) &&
-        (c->opt_rounds == 2 || (c->opt_rounds == 1 && n >= kOrderMinN))) {
+        (c->opt_rounds == 2 || (rounds && n >= kOrderMinN))) {
         const int columns = plan_order(c, n, linkage);
         if (columns) return run_order(c, dist, n, linkage, out, flags, columns, s);
     }

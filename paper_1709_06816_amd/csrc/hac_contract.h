@@ -13,6 +13,14 @@ namespace hac {
 constexpr int kContractBlock = 1024;   // threads per workgroup
 constexpr int kContractMaxN = 32768;   // a row fits one workgroup's registers and LDS
 
+// Workgroups that m clusters keep busy, of at most G: the barriers of fewer cost
+// less (n = 512: 327 us for the call on 256, 330 on 64, 340 on 16, 365 on 8; n = 1500: 423 on
+// 256, 428 on 128, 437 on 64; n = 150: 257 on 256, 249 on 16).
+__host__ __device__ constexpr int contract_workgroups(int m, int G) {
+    const int k = m > 4096 ? G : m > 1024 ? 128 : m > 256 ? 64 : m > 64 ? 16 : 4;
+    return k < G ? k : G;
+}
+
 struct ContractCtl {
     uint32_t bar;                      // grid barrier arrivals (monotonic)
     uint32_t abort;                    // set by a workgroup that gives up

@@ -741,8 +741,7 @@ __global__ __launch_bounds__(B) void k_contract(Args A) {
             __syncthreads();  // every wave reads the whole mask next
         }
         }
-        // Fewer workgroups as the rows get fewer: the barriers cost less.
-        const int keep = m > 4096 ? G : min(G, m > 1024 ? 128 : m > 256 ? 64 : m > 64 ? 16 : 4);
+        const int keep = contract_workgroups(m, G);  // the others leave
         if (w >= keep) return;
         G = keep;
         if (may_hand_over && round >= kWindow && n - merges > kHandoverLeft && recent < kWindow * kMinPerRound) {

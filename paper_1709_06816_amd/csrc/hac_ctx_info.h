@@ -1,4 +1,5 @@
-// What the serving layer needs to know about a context (internal).
+// What the serving layer and the other entry points need to know about each
+// other (internal).
 #pragma once
 #include <stddef.h>
 #include <stdint.h>
@@ -16,5 +17,8 @@ struct CtxInfo {
     bool lazy;           // HAC_OPT_LAZY_MIRROR
 };
 void ctx_info(const hac_ctx *c, CtxInfo *out);
+
+// Compute units of a device that this process's serving kernels hold at the moment.
+int serving_cus(int device);
 
 }  // namespace hac

@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <chrono>
 #include <condition_variable>
 #include <cstdarg>
@@ -100,6 +101,7 @@ struct hac_server {
     hipStream_t kern = nullptr;
     hipEvent_t kern_done = nullptr;
     bool kern_running = false;
+    int held = 0;              // compute units that the running kernel holds
     int64_t launches = 0;
     uint64_t stopped_at = 0;  // entries consumed when the kernel last stopped
 
@@ -187,6 +189,17 @@ size_t page_bytes(const hac_server *s) {
     return align_up(sizeof(hac::ServeDev), kAlign) + align_up(sizeof(hac::Control), kAlign);
 }
 
+// Compute units held by all serving kernels of the process, by device (devices
+// beyond the last word share it).
+std::atomic<int> g_held[64];
+std::atomic<int> &held_on(int device) { return g_held[std::min(std::max(device, 0), 63)]; }
+
+void set_running(hac_server *s, bool on) {
+    if (s->kern_running == on) return;
+    s->kern_running = on;
+    held_on(s->info.device).fetch_add(on ? s->held : -s->held);
+}
+
 // Copy the launch image of the device words (head = tail = entries already
 // consumed, no token, no stop, zeroed counters) and launch the kernel.
 int launch_kernel(hac_server *s) {
@@ -212,7 +225,7 @@ int launch_kernel(hac_server *s) {
     if (e != hipSuccess) return sdevice(s, e, "serving kernel launch");
     e = hipEventRecord(s->kern_done, s->kern);
     if (e != hipSuccess) return sdevice(s, e, "serving kernel event");
-    s->kern_running = true;
+    set_running(s, true);
     s->launches++;
     s->launched_at = std::chrono::steady_clock::now();
     return HAC_OK;
@@ -224,7 +237,7 @@ int stop_kernel(hac_server *s) {
     __atomic_store_n(&s->host->stop, 1u, __ATOMIC_RELEASE);
     hipError_t e = hipEventSynchronize(s->kern_done);
     __atomic_store_n(&s->host->stop, 0u, __ATOMIC_RELEASE);
-    s->kern_running = false;
+    set_running(s, false);
     s->stopped_at = s->published;
     if (e != hipSuccess) return sdevice(s, e, "serving kernel");
     return HAC_OK;
@@ -369,7 +382,7 @@ void worker_loop(hac_server *s) {
             // The kernel stops by itself only after a long idle period.
             const hipError_t q = hipEventQuery(s->kern_done);
             if (q != hipErrorNotReady) {
-                s->kern_running = false;
+                set_running(s, false);
                 s->stopped_at = s->published;
                 if (q != hipSuccess) sdevice(s, q, "serving kernel");
                 else if (!s->running.empty()) {
@@ -434,6 +447,12 @@ void free_server(hac_server *s) {
 
 }  // namespace
 
+namespace hac {
+
+int serving_cus(int device) { return held_on(device).load(); }
+
+}  // namespace hac
+
 extern "C" {
 
 int hac_server_create(hac_ctx *ctx, size_t hbm_budget_bytes, int32_t max_jobs, int32_t max_n,
@@ -468,7 +487,8 @@ int hac_server_create(hac_ctx *ctx, size_t hbm_budget_bytes, int32_t max_jobs, i
     // per XCD free so that copy kernels the runtime may use for host
     // transfers, and other work on the device, can run beside the kernel.
     const int reserve = std::max(kXcds, s->info.cus / 32);
-    s->grid = std::max(1, hac::serve_occupancy(lds, s->block)) * std::max(1, s->info.cus - reserve);
+    s->held = std::max(1, s->info.cus - reserve);
+    s->grid = std::max(1, hac::serve_occupancy(lds, s->block)) * s->held;
     if (group_for(max_n, s->info.lds_max) > s->grid) {
         free_server(s);
         return HAC_EINVAL;
