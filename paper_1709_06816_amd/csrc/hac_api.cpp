@@ -93,6 +93,7 @@ struct hac_ctx {
     int64_t opt_rounds = 1;
     int64_t opt_stall = 0;
     bool opt_lazy = true;  // HAC_OPT_LAZY_MIRROR
+    bool in_place = false;  // hac_internal_rounds_in_place
     int pending_plan_source = 0, pending_plan_share = 0, pending_plan_upd = 0;  // hac_batch: its plan
     std::unordered_map<std::string, hipGraphExec_t> graphs;  // batch graphs by layout
 
@@ -701,6 +702,12 @@ int hac_get_stats(const hac_ctx *c, hac_stats *out) {
     return HAC_OK;
 }
 
+int hac_internal_rounds_in_place(hac_ctx *c, int on) {
+    if (!c) return HAC_EINVAL;
+    c->in_place = on != 0;
+    return HAC_OK;
+}
+
 int hac_sync(hac_ctx *c) {
     if (!c) return HAC_EINVAL;
     if (!c->pending) return HAC_OK;
@@ -765,7 +772,7 @@ int plan_seq(hac_ctx *c, int32_t n, uint32_t flags, bool noalloc, int *g_out, in
 int run_rounds(hac_ctx *c, float *dist, int32_t n, int32_t linkage, hac_merge *out, uint32_t flags, hipStream_t s) {
     if (!c->coop) return fail(c, HAC_EDEVICE, "device does not support cooperative launch");
     // On a shrinking matrix where a row fits a workgroup, in place above.
-    const bool contract = n <= hac::kContractMaxN && hac::contract_occupancy(linkage) > 0;
+    const bool contract = !c->in_place && n <= hac::kContractMaxN && hac::contract_occupancy(linkage) > 0;
     int G = contract ? hac::contract_workgroups(n, c->cus) : c->cus * hac::rounds_occupancy();
     if (c->opt_wgs > 0) G = std::min(G, (int)c->opt_wgs);
     // Automatic mode: the one-merge-per-step kernel is queued behind the

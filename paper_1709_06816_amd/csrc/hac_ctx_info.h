@@ -18,6 +18,10 @@ struct CtxInfo {
 };
 void ctx_info(const hac_ctx *c, CtxInfo *out);
 
+// Tests: single and complete linkage by rounds of this context in place at every size
+// (on = 1), not only above kContractMaxN (0, the default).  Not part of hac.h.
+extern "C" int hac_internal_rounds_in_place(hac_ctx *c, int on);
+
 // Compute units of a device that this process's serving kernels hold at the moment.
 int serving_cus(int device);
 
