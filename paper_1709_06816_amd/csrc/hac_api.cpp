@@ -80,8 +80,7 @@ struct hac_ctx {
     size_t dout_cap = 0;         // records
     void *pinned = nullptr;      // host staging (status read-back, descriptor upload)
     size_t pinned_cap = 0;
-    void *recs = nullptr;        // host staging of merge records
-    size_t recs_cap = 0;
+    void *recs = nullptr;        // host staging of merge records: kStagedRecords bytes, or null
     hipEvent_t ev[4] = {nullptr, nullptr, nullptr, nullptr};  // [3]: end of the round engine's kernel
 
     hac_stats stats{};
@@ -183,21 +182,10 @@ int ensure_pinned(hac_ctx *c, size_t need) {
     return HAC_OK;
 }
 
-// Page-locked room for merge records (grown on demand, up to kStagedRecords).
+// Merge records up to this size come back through the context's page-locked
+// room.  It is allocated once, whole: growing it would free page-locked memory
+// inside a call, which waits for everything on the device.
 constexpr size_t kStagedRecords = (size_t)2 << 20;
-int ensure_records(hac_ctx *c, size_t need) {
-    if (need <= c->recs_cap) return HAC_OK;
-    void *p = nullptr;
-    const size_t sz = std::min(kStagedRecords, std::max(need, (size_t)65536));
-    if (hipHostMalloc(&p, sz, hipHostMallocDefault) != hipSuccess) {
-        (void)hipGetLastError();
-        return HAC_ENOMEM;
-    }
-    if (c->recs) (void)hipHostFree(c->recs);  // idle: every copy into it is waited for
-    c->recs = p;
-    c->recs_cap = sz;
-    return HAC_OK;
-}
 
 int set_device(hac_ctx *c) {
     HIP_TRY(c, hipSetDevice(c->device));
@@ -297,7 +285,7 @@ int finish(hac_ctx *c, hipStream_t s, int nstatus, hac_merge *out, size_t nrec, 
     // where there are not too many of them: one wait instead of two (n=100:
     // 25 us less), and on an error out stays as it was.
     const size_t rec_bytes = nrec * sizeof(hac_merge);
-    const bool staged = nrec && rec_bytes <= kStagedRecords && ensure_records(c, rec_bytes) == HAC_OK;
+    const bool staged = nrec && c->recs && rec_bytes <= kStagedRecords;
     if (staged) HIP_TRY(c, hipMemcpyAsync(c->recs, c->dout, rec_bytes, hipMemcpyDeviceToHost, s));
     HIP_TRY(c, hipStreamSynchronize(s));
     c->pending = false;
@@ -598,6 +586,10 @@ int hac_create(int device, hac_ctx **out) {
     if (ensure_pinned(c, 4096) != HAC_OK) {
         hac_destroy(c);
         return HAC_EDEVICE;
+    }
+    if (hipHostMalloc(&c->recs, kStagedRecords, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();  // records then come back by a copy of their own
+        c->recs = nullptr;
     }
     *out = c;
     return HAC_OK;
