@@ -8,7 +8,7 @@ ROOT = os.path.dirname(HERE)
 LIB = os.path.join(HERE, "libhac.so")
 SOURCES = [os.path.join(HERE, "csrc", f) for f in ("hac_engine.hip", "hac_rounds.hip", "hac_order.hip", "hac_small.hip", "hac_contract.hip", "hac_scan.hip", "hac_rmsd.hip", "hac_api.cpp",
                                                    "hac_serve.cpp", "hac_validate.cpp")]
-HEADERS = [os.path.join(HERE, "csrc", f) for f in ("hac_engine.h", "hac_dev.h", "hac_rounds.h", "hac_order.h", "hac_small.h", "hac_contract.h", "hac_ctx_info.h",
+HEADERS = [os.path.join(HERE, "csrc", f) for f in ("hac_engine.h", "hac_dev.h", "hac_rounds.h", "hac_order.h", "hac_slots.h", "hac_small.h", "hac_contract.h", "hac_ctx_info.h",
                                                    "hac_arena.h", "hac_rmsd.h", "hac_qcp.h", "hac_validate.h", "hac_scan.h")] + [
     os.path.join(ROOT, "include", "hac.h")]
 

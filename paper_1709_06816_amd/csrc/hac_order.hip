@@ -50,6 +50,7 @@
 
 #include "hac_dev.h"
 #include "hac_order.h"
+#include "hac_slots.h"
 
 namespace hac {
 namespace {
@@ -502,9 +503,11 @@ __global__ __launch_bounds__(B) void k_order(OrderArgs A) {
         uint64_t *base = A.slots + (size_t)(e & 1u) * (G + 2) * kOrderSlotWords;
         uint64_t *cast = base + (size_t)G * kOrderSlotWords;
         clk.lap(kPhCand);
-        if (G > 1 && tid < units && !((A.flags & kFlagStall) && w == 0)) {
+        if (G > 1 && tid < (writes_whole_slot(e) ? kOrderUnits : units) && !((A.flags & kFlagStall) && w == 0)) {
             uint64_t a, b;
-            if (tid == 0) {
+            if (tid >= units) {
+                a = b = gen;  // read by nobody
+            } else if (tid == 0) {
                 a = ((uint64_t)pT << 32) | gen;
                 b = ((uint64_t)s_pTE << 32) | gen;
             } else if (tid < 2 + KC) {
@@ -637,9 +640,11 @@ __global__ __launch_bounds__(B) void k_order(OrderArgs A) {
                 }
             }
             if (G > kOrderAllToAll) __syncthreads();
-            if (G > kOrderAllToAll && tid < 1 + KP + pprev) {
+            if (G > kOrderAllToAll && tid < 1 + KP + (writes_whole_slot(e) ? KP : pprev)) {
                 uint64_t a, b;
-                if (tid == 0) {
+                if (tid >= 1 + KP + pprev) {
+                    a = b = gen;
+                } else if (tid == 0) {
                     a = ((uint64_t)TE << 32) | ((uint64_t)p << 16) | gen;
                     b = ((uint64_t)smin << 32) | gen;
                 } else if (tid < 1 + KP) {
