@@ -9,6 +9,9 @@
 namespace hac {
 
 constexpr int kSmallMaxN = 192;  // 192 x 193 floats of LDS
+// Row pitch of the matrix in LDS: odd, so that a column's entries fall into banks of
+// their own as a row's do.
+__host__ __device__ constexpr int small_pitch(int n) { return n | 1; }
 
 // LDS limit of the kernel; call once per device.
 hipError_t small_setup();

@@ -3,7 +3,7 @@
 //
 // At these sizes a merge is a chain of dependent steps over a few hundred
 // values, so what counts is the latency of each step: the matrix in LDS
-// (row pitch n + 1: rows and columns are both free of bank conflicts) saves the
+// (odd row pitch: rows and columns are both free of bank conflicts) saves the
 // trips to L2, one wave saves the barriers, and one launch does what five did.
 // Sixteen waves load and check the input; then wave 0 goes on alone, each of
 // its lanes keeping up to three rows' minima in registers.
@@ -56,7 +56,7 @@ __device__ __forceinline__ int winner(uint32_t mine, uint32_t tie, uint32_t &o) 
 template <int link, int R>
 __global__ __launch_bounds__(B) void k_small(const float *__restrict__ src, int n, hac_merge *__restrict__ out,
                                              uint32_t *status, Control *ctl) {
-    const int tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6, P = n + 1;
+    const int tid = (int)threadIdx.x, lane = tid & 63, wv = tid >> 6, P = small_pitch(n);
     if (tid == 0) s_bad = 0;
     __syncthreads();
     // ---- load, check and mirror the strict upper triangle --------------------
@@ -288,7 +288,7 @@ const void *small_kernel(int link, int rows) {
     }
 }
 
-constexpr size_t small_lds(int n) { return (size_t)n * (n + 1) * 4; }
+constexpr size_t small_lds(int n) { return (size_t)n * small_pitch(n) * 4; }
 
 }  // namespace
 
