@@ -102,6 +102,8 @@ struct hac_ctx {
     int pending_count = 0;           // status words to check
     int pending_wgs = 0, pending_block = 0, pending_group = 0, pending_graph = 0, pending_deferred = 0;
     bool pending_rounds = false;
+    bool pending_order = false;
+    int32_t ordered_rounds = 0, ordered_handed = 0;  // hac_internal_ordered_rounds
     bool pending_scan = false;
     int pending_seq_wgs = 0, pending_seq_block = 0, pending_seq_deferred = 0;  // kernel queued behind the rounds
 };
@@ -229,6 +231,8 @@ int check_status(hac_ctx *c) {
     c->stats.deferred = c->pending_deferred;
     c->stats.rounds = c->pending_rounds ? (int32_t)ctl->rounds : 0;
     c->stats.compactions = c->pending_scan ? (int32_t)ctl->rounds : 0;
+    c->ordered_rounds = c->pending_order ? (int32_t)ctl->rounds : 0;
+    c->ordered_handed = c->pending_order && (st[0] & hac::kHandover) ? 1 : 0;
     c->stats.rounds_ms = 0.0;
     c->stats.rounds_rescan_elems = c->stats.rounds_update_elems = 0;
     if (c->pending_rounds) {
@@ -700,6 +704,13 @@ int hac_internal_rounds_in_place(hac_ctx *c, int on) {
     return HAC_OK;
 }
 
+int hac_internal_ordered_rounds(const hac_ctx *c, int32_t *rounds, int32_t *handed_over) {
+    if (!c || !rounds || !handed_over) return HAC_EINVAL;
+    *rounds = c->ordered_rounds;
+    *handed_over = c->ordered_handed;
+    return HAC_OK;
+}
+
 int hac_sync(hac_ctx *c) {
     if (!c) return HAC_EINVAL;
     if (!c->pending) return HAC_OK;
@@ -960,6 +971,7 @@ int run_order(hac_ctx *c, float *dist, int32_t n, int32_t linkage, hac_merge *ou
     c->pending_graph = 0;
     c->pending_plan_source = c->pending_plan_share = c->pending_plan_upd = 0;
     c->pending_deferred = 0;
+    c->pending_order = true;
     return finish(c, s, 1, out, (flags & HAC_OUT_DEVICE) ? 0 : (size_t)(n - 1), flags, ws);
 }
 
@@ -1074,8 +1086,8 @@ int run_impl(hac_ctx *c, float *dist, int32_t n, int32_t linkage, hac_merge *out
     }
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     c->stats = hac_stats{};
-    c->pending_rounds = false;
-    c->pending_scan = false;
+    c->pending_rounds = c->pending_order = c->pending_scan = false;
+    c->ordered_rounds = c->ordered_handed = 0;
     if (n == 1) return HAC_OK;
     // Small instances, unless an option asks for another split of the work
     // (whole call, small kernel / otherwise: average n=100 149 / 358 us, n=192
@@ -1303,8 +1315,7 @@ int hac_batch(hac_ctx *c, float *packed, const int64_t *offsets, const int32_t *
     c->pending_plan_upd = plan_update(plan);
     c->pending_graph = graphed;
     c->pending_deferred = 1;
-    c->pending_rounds = false;
-    c->pending_scan = false;
+    c->pending_rounds = c->pending_order = c->pending_scan = false;
     return finish(c, s, count, out, (flags & HAC_OUT_DEVICE) ? 0 : (size_t)rec_extent, flags, c->ws);
 }
 
