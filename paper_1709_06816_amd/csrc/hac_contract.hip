@@ -56,6 +56,17 @@ constexpr uint32_t kTied = 0x8000u;          // nearest-neighbour entry: the min
 constexpr int kWindow = 8;                   // hand-over, as in hac_rounds.hip
 constexpr int kMinPerRound = 12;
 constexpr int kHandoverLeft = 96;            // the last merges are made here: they cost little
+// Up to this size the kernel behind is one workgroup, a merge there cheaper, and the
+// hand-over (its start, the rows back to their slots) dear: from the second round on
+// what is left is priced both ways, at the last rounds' pace (eight rounds below 12
+// pairs and 96 merges left / this rule / one merge per step alone: single linkage,
+// uniform values, n = 208 1.12 / 0.49 / 0.62 ms, RMSD-like n = 320 0.82 / 0.45 / 0.99, 50
+// distinct values n = 320 1.04 / 0.97 / 0.75).
+constexpr int kSmallN = 1536;
+__device__ __forceinline__ bool cheaper_behind(int recent, int rounds, int left, int n) {
+    const float merge_us = fminf(4.5f, 1.3f + 0.004f * (float)n), round_us = 12.0f, start_us = 150.0f;
+    return (float)left * (round_us * (float)rounds - merge_us * (float)recent) > start_us * (float)recent;
+}
 
 constexpr int kWideMin = 4096;
 constexpr int kInplaceMin = 1024;            // smaller matrices are contracted every round
@@ -744,7 +755,10 @@ __global__ __launch_bounds__(B) void k_contract(Args A) {
         const int keep = contract_workgroups(m, G);  // the others leave
         if (w >= keep) return;
         G = keep;
-        if (may_hand_over && round >= kWindow && n - merges > kHandoverLeft && recent < kWindow * kMinPerRound) {
+        const bool few = n <= kSmallN ? round >= 2 && cheaper_behind(recent, min(round, kWindow), n - merges, n)
+                                      : round >= kWindow && n - merges > kHandoverLeft &&
+                                            recent < kWindow * kMinPerRound;
+        if (may_hand_over && few) {
             leave = kHandover;
             break;
         }

@@ -441,7 +441,9 @@ __global__ __launch_bounds__(B) void k_order(OrderArgs A) {
     int merges = 0, round = 0, p = 0, qidx = -1;
     uint32_t TE = 0, smin = 0;  // of the last exchange: smallest exact second entry, smallest pair's value
     bool stuck = false;         // it found no merge
-    int pace = 16 << 8;  // merges per round, running mean over about 16 rounds (8 fractional bits)
+    // Merges per round, running mean over about 16 rounds (8 fractional bits), from
+    // what clustered points of this many items make.
+    int pace = (int)(256.0f * fminf(16.0f, fmaxf(3.0f, 0.2f * sqrtf((float)n))));
     bool negative = false;
     const bool may_hand_over = !(A.flags & kFlagNoHandover);
     const int nseg = (n + kSegCols - 1) / kSegCols;
