@@ -846,12 +846,12 @@ int run_rounds(hac_ctx *c, float *dist, int32_t n, int32_t linkage, hac_merge *o
     const int rflags = (c->opt_profile ? hac::kFlagProfile : 0) | (handover ? 0 : hac::kFlagNoHandover) |
                        (c->opt_stall ? hac::kFlagStall : 0);
     hac::Control *ctl = reinterpret_cast<hac::Control *>(ws);
-    hipError_t e = contract ? hac::launch_contract(D, n, linkage, inst.status, ctl, ws + ro_off, G, timeout_ticks(c),
-                                                   rflags | (inplace_next ? hac::kFlagInplaceNext : 0), s)
-                            : hac::launch_rounds(D, n, linkage, inst.status, ctl, ws + ro_off, Lr, G,
+    hipError_t e = contract ? hac::launch_contract(D, n, linkage, inst.status, ctl, inst.rowkey, ws + ro_off, G,
+                                                   timeout_ticks(c), rflags | (inplace_next ? hac::kFlagInplaceNext : 0), s)
+                            : hac::launch_rounds(D, n, linkage, inst.status, ctl, inst.rowkey, ws + ro_off, Lr, G,
                                                  timeout_ticks(c), rflags, s);
     if (e == hipSuccess && inplace_next)
-        e = hac::launch_rounds(D, n, linkage, inst.status, ctl, ws + ro_off, Lr, Gr, timeout_ticks(c),
+        e = hac::launch_rounds(D, n, linkage, inst.status, ctl, inst.rowkey, ws + ro_off, Lr, Gr, timeout_ticks(c),
                                rflags | hac::kFlagAfterRounds, s);
     if (e != hipSuccess) return hip_fail(c, e, "round kernel launch");
     HIP_TRY(c, hipEventRecord(c->ev[3], s));
@@ -949,14 +949,14 @@ int run_order(hac_ctx *c, float *dist, int32_t n, int32_t linkage, hac_merge *ou
     hac::Control *ctl = reinterpret_cast<hac::Control *>(ws);
     HIP_TRY(c, hipEventRecord(c->ev[0], s));
     HIP_TRY(c, hac::launch_zero(ws, (st_off + st_bytes) / 4, s));
-    // The slots of both kernels lie next to each other.
-    HIP_TRY(c, hac::launch_zero(ws + or_off + Lo.slots, (Lo.bytes - Lo.slots + sl_bytes) / 4, s));
+    // The state word and the slots of both kernels lie next to each other.
+    HIP_TRY(c, hac::launch_zero(ws + or_off + Lo.state, (Lo.bytes - Lo.state + sl_bytes) / 4, s));
     HIP_TRY(c, hac::launch_setup(inst, dist, s));
     HIP_TRY(c, hipEventRecord(c->ev[1], s));
     const int oflags = (c->opt_profile ? hac::kFlagProfile : 0) | (handover ? 0 : hac::kFlagNoHandover) |
                        (c->opt_stall ? hac::kFlagStall : 0);
-    hipError_t e = hac::launch_order(D, n, linkage, dev_out, inst.status, ctl, ws + or_off, columns, timeout_ticks(c),
-                                     oflags, s);
+    hipError_t e = hac::launch_order(D, n, linkage, dev_out, inst.status, ctl, inst.rowkey, ws + or_off, columns,
+                                     timeout_ticks(c), oflags, s);
     if (e != hipSuccess) return hip_fail(c, e, "ordered-round kernel launch");
     if (handover) {
         // Resumes from the ordered rounds' state if they hand over.

@@ -46,7 +46,8 @@ int contract_occupancy(int link);
 // kFlagInplaceNext in `flags` (complete linkage) leaves the rest to a launch_rounds
 // queued behind it on the layout contract_rounds_layout (kInplace in `status`) when
 // rounds have too few pairs to stream the matrix for them.
-hipError_t launch_contract(float *D, int n, int link, uint32_t *status, Control *ctl, void *ws, int G,
+// At a hand-over the live rows' minima go to `rowkey` (Instance::rowkey).
+hipError_t launch_contract(float *D, int n, int link, uint32_t *status, Control *ctl, uint64_t *rowkey, void *ws, int G,
                            uint64_t timeout_ticks, int flags, hipStream_t stream);
 Resume contract_resume(int n, void *ws);
 // Workspace of that launch_rounds, on the same base: its own words follow the

@@ -123,6 +123,7 @@ struct Args {
     uint64_t *key;
     uint32_t *live;       // hand-over: live mask and sizes by slot
     int32_t *hsize;
+    uint64_t *rowkey;     //   and the live rows' minima over the live columns to their right
     uint64_t timeout;
     int n, flags;
 };
@@ -766,15 +767,29 @@ __global__ __launch_bounds__(B) void k_contract(Args A) {
     if (leave) {
         __syncthreads();
         // Rows back to their columns' slots for the kernel that goes on (they are
-        // still there before the first contraction).
-        for (int q = w; q < m && m < n; q += G) {
+        // still there before the first contraction), and their minima for k_run.
+        const bool moved = m < n;
+        for (int q = w; q < m && (moved || leave == kHandover); q += G) {
             if ((dead[q >> 6] >> (q & 63)) & 1ull) continue;
             const int s = A.slot[par][q];
             const float *from = row_at(D, n, s, aligned);
             float *p = D + (size_t)s * n;
-            for (int c = tid; c < m; c += B) row[c] = __float_as_uint(from[c]);
+            uint64_t best = kNone;
+            for (int c = tid; c < m; c += B) {
+                const float x = from[c];
+                row[c] = __float_as_uint(x);
+                if (c > q && !((dead[c >> 6] >> (c & 63)) & 1ull))
+                    best = umin64(best, ((uint64_t)ord32(x) << 32) | ((uint64_t)A.slot[par][c] << 16));
+            }
+            best = wave_min64(best);
+            if (lane == 0) s_key[0][wv] = best;
             __syncthreads();
-            for (int c = tid; c < m; c += B) p[A.slot[par][c]] = __uint_as_float(row[c]);
+            if (moved)
+                for (int c = tid; c < m; c += B) p[A.slot[par][c]] = __uint_as_float(row[c]);
+            if (tid == 0) {
+                for (int k = 1; k < W; ++k) best = umin64(best, s_key[0][k]);
+                A.rowkey[s] = best;
+            }
             __syncthreads();
         }
         __syncthreads();
@@ -795,6 +810,11 @@ __global__ __launch_bounds__(B) void k_contract(Args A) {
             if (tid == 0) {
                 A.cc->merges = (uint32_t)merges;
                 A.cc->round = (uint32_t)round;
+                if (leave == kHandover) {
+                    const unsigned long long left = (unsigned long long)(n - merges);
+                    atomicAdd(&A.ctl->rescans, left);
+                    atomicAdd(&A.ctl->rescan_elems, left * (left - 1) / 2);
+                }
                 atomicOr(A.status, leave);
             }
         }
@@ -859,7 +879,7 @@ int contract_occupancy(int link) {
     return blocks;
 }
 
-hipError_t launch_contract(float *D, int n, int link, uint32_t *status, Control *ctl, void *ws, int G,
+hipError_t launch_contract(float *D, int n, int link, uint32_t *status, Control *ctl, uint64_t *rowkey, void *ws, int G,
                            uint64_t timeout_ticks, int flags, hipStream_t stream) {
     const ContractLayout Lo = contract_layout(n);
     char *b = static_cast<char *>(ws);
@@ -882,6 +902,7 @@ hipError_t launch_contract(float *D, int n, int link, uint32_t *status, Control 
     a.key = reinterpret_cast<uint64_t *>(b + Lo.key);
     a.live = reinterpret_cast<uint32_t *>(b + Lo.live);
     a.hsize = reinterpret_cast<int32_t *>(b + Lo.hsize);
+    a.rowkey = rowkey;
     a.timeout = timeout_ticks;
     a.n = n;
     a.flags = flags;

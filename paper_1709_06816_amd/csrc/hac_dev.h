@@ -130,6 +130,31 @@ __device__ __forceinline__ uint64_t wave_min64(uint64_t v) {
            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, 63);
 }
 
+// One wave: the smallest entry (ord:32 | column:16 | 0:16) of row r of the n x n
+// matrix over the live columns to its right, all ones if there is none; every lane
+// gets it.
+__device__ __forceinline__ uint64_t upper_row_min(const float *__restrict__ D, int n, int r, const uint32_t *live) {
+    constexpr int U = 8;  // loads in flight
+    const float *row = D + (size_t)r * n;
+    const int lane = (int)(threadIdx.x & 63);
+    uint64_t best = ~0ull;
+    for (int c0 = r + 1; c0 < n; c0 += 64 * U) {
+        float x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int c = c0 + u * 64 + lane;
+            x[u] = c < n ? row[c] : 0.0f;
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int c = c0 + u * 64 + lane;
+            if (c < n && ((live[c >> 5] >> (c & 31)) & 1u))
+                best = umin64(best, ((uint64_t)ord32(x[u]) << 32) | ((uint64_t)c << 16));
+        }
+    }
+    return wave_min64(best);
+}
+
 // Grid barrier of a cooperative launch of G workgroups: every workgroup's
 // writes before it are visible to every workgroup after it (stores complete,
 // then an agent-scope release, a monotonic arrival counter *bar, an

@@ -903,25 +903,16 @@ __global__ __launch_bounds__(B) void k_run(Instance I, Control *ctl, uint64_t ti
         merge_loop<B, kMode>(I, g, w, L, ctl, timeout, st, 0u);
     } else {
         // Resume where the round engine stopped: its live slots and sizes,
-        // and every own live row's minimum over the live columns to its
-        // right, rescanned from the current matrix.
+        // and the minima that it left of the live rows.
         const int s0 = (int)rs.state[0], round0 = (int)rs.state[1];
         const int mask_words = (n + 31) >> 5;
         for (int q = threadIdx.x; q < mask_words; q += B) L.amask[q] = rs.live[q];
         for (int k = threadIdx.x; k < n; k += B) L.size1[k] = (uint16_t)(rs.size[k] - 1);
-        if (threadIdx.x == 0) s_nresc = 0;
         __syncthreads();
         for (int li = threadIdx.x; li < own_cap; li += B) {
             const int k = row_of_local(li, g, w);
-            L.cache[li] = kEmptyRow;
-            if (li < own_ch * 64 && k < n && is_live(L.amask, k)) L.rlist[atomicAdd(&s_nresc, 1u)] = (uint16_t)li;
-        }
-        __syncthreads();
-        rescan_rows<B>(I.D, n, g, w, L, s_nresc, -1, st.rescan_elems);
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            st.rescans += s_nresc;
-            s_nresc = 0;
+            const uint64_t v = li < own_ch * 64 && k < n && is_live(L.amask, k) ? I.rowkey[k] : kEmpty;
+            L.cache[li] = v == kEmpty ? kEmptyRow : v;
         }
         __syncthreads();
         merge_loop<B, kMode>(I, g, w, L, ctl, timeout, st, 0u, s0, rs.keys, round0);

@@ -34,10 +34,11 @@ int order_occupancy(int n, int columns, int link);
 // ceil(n / columns) co-resident workgroups.  Records go to `out` in merge
 // order.  With kFlagNoHandover in `flags` it makes every merge; otherwise it
 // leaves the rest to a k_run launch queued behind it (kHandover in `status`,
-// state from order_resume) when rounds make few merges each.
-// The workspace's slots must be zero.
-hipError_t launch_order(float *D, int n, int link, hac_merge *out, uint32_t *status, Control *ctl, void *ws,
-                        int columns, uint64_t timeout_ticks, int flags, hipStream_t stream);
+// state from order_resume, the live rows' minima in `rowkey`) when rounds make
+// few merges each.
+// The workspace must be zero from `state` on.
+hipError_t launch_order(float *D, int n, int link, hac_merge *out, uint32_t *status, Control *ctl, uint64_t *rowkey,
+                        void *ws, int columns, uint64_t timeout_ticks, int flags, hipStream_t stream);
 Resume order_resume(int n, int G, void *ws);
 
 }  // namespace hac

@@ -74,7 +74,8 @@ struct OrderArgs {
     uint64_t *vsize;   // n cluster sizes with the round that last changed them (size_word)
     int32_t *size;     // n cluster sizes left at a hand-over
     uint32_t *live;    // live mask left at a hand-over
-    uint32_t *state;   // [0] merges, [1] rounds at a hand-over
+    uint32_t *state;   // [0] merges, [1] rounds at a hand-over; [2] workgroups arrived there
+    uint64_t *rowkey;  // the live rows' minima over the columns to their right, left at a hand-over
     uint64_t *slots;   // 2 * (G + 2) * kOrderSlotWords: G slots, then workgroup 0's list (two slots' room)
     uint64_t timeout;
     int n, flags;
@@ -938,13 +939,24 @@ __global__ __launch_bounds__(B) void k_order(OrderArgs A) {
         ++round;
         if (may_hand_over && n - 1 - merges > kHandoverLeft) {
             if (pace < kHandoverPace) {
-                __syncthreads();
+                // Own rows' minima, once every workgroup's entries are written.
+                uint32_t arrived = 0;
+                if (!grid_sync(A.state + 2, &A.ctl->abort, &A.ctl->error, kErrTimeout, arrived, (uint32_t)G, A.timeout))
+                    return;
                 if (tid < C && c < n) A.size[c] = L.csize[tid];
+                for (int r = w * C + wv; r < min(n, (w + 1) * C); r += W) {
+                    if (!bit(L.amask, r)) continue;
+                    const uint64_t v = upper_row_min(D, n, r, L.amask);
+                    if (lane == 0) A.rowkey[r] = v;
+                }
                 if (w == 0) {
                     for (int q = tid; q < words; q += B) A.live[q] = L.amask[q];
                     if (tid == 0) {
                         A.state[0] = (uint32_t)merges;
                         A.state[1] = (uint32_t)round;
+                        const unsigned long long left = (unsigned long long)(n - merges);
+                        atomicAdd(&A.ctl->rescans, left);
+                        atomicAdd(&A.ctl->rescan_elems, left * (left - 1) / 2);
                         atomicOr(A.status, kHandover);
                     }
                 }
@@ -1034,8 +1046,8 @@ int order_occupancy(int n, int columns, int link) {
     return blocks;
 }
 
-hipError_t launch_order(float *D, int n, int link, hac_merge *out, uint32_t *status, Control *ctl, void *ws,
-                        int columns, uint64_t timeout_ticks, int flags, hipStream_t stream) {
+hipError_t launch_order(float *D, int n, int link, hac_merge *out, uint32_t *status, Control *ctl, uint64_t *rowkey,
+                        void *ws, int columns, uint64_t timeout_ticks, int flags, hipStream_t stream) {
     const int G = (n + columns - 1) / columns;
     const OrderLayout Lo = order_layout(n, G);
     char *b = static_cast<char *>(ws);
@@ -1051,6 +1063,7 @@ hipError_t launch_order(float *D, int n, int link, hac_merge *out, uint32_t *sta
     a.live = reinterpret_cast<uint32_t *>(b + Lo.live);
     a.state = reinterpret_cast<uint32_t *>(b + Lo.state);
     a.slots = reinterpret_cast<uint64_t *>(b + Lo.slots);
+    a.rowkey = rowkey;
     a.timeout = timeout_ticks;
     a.n = n;
     a.flags = flags;

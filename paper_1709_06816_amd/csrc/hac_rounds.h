@@ -53,8 +53,9 @@ int rounds_occupancy();
 // Errors and statistics go to `ctl` (rescans, rescan_elems, update_elems,
 // rounds; with kFlagProfile in `flags`, per-workgroup phase times: [0] first
 // rescans, [1] grid barriers, [2] updates, [3] rescans, [4] pair detection).
-hipError_t launch_rounds(float *D, int n, int link, uint32_t *status, Control *ctl, void *ws, const RoundsLayout &Lo,
-                         int G, uint64_t timeout_ticks, int flags, hipStream_t stream);
+// At a hand-over the live rows' minima go to `rowkey` (Instance::rowkey).
+hipError_t launch_rounds(float *D, int n, int link, uint32_t *status, Control *ctl, uint64_t *rowkey, void *ws,
+                         const RoundsLayout &Lo, int G, uint64_t timeout_ticks, int flags, hipStream_t stream);
 
 // Hand-over state inside a round-engine workspace (for launch_merge).
 Resume rounds_resume(const RoundsLayout &Lo, void *ws);

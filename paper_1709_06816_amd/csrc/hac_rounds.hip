@@ -248,8 +248,8 @@ constexpr int kWindow = 8;
 constexpr int kMinPerRound = 12;
 
 __global__ __launch_bounds__(kRoundsBlock) void k_rounds(float *D, int n, int link, uint32_t *status,
-                                                         Control *ctl, char *ws, RoundsLayout Lo, uint64_t timeout,
-                                                         int flags) {
+                                                         Control *ctl, uint64_t *rowkey, char *ws, RoundsLayout Lo,
+                                                         uint64_t timeout, int flags) {
     const Views V = views(ws, Lo);
     Clock clk{(flags & kFlagProfile) != 0};
     if (clk.on && threadIdx.x == 0) clk.mark = wall_clock64();
@@ -302,11 +302,19 @@ __global__ __launch_bounds__(kRoundsBlock) void k_rounds(float *D, int n, int li
             for (int t = 0; t < kWindow; ++t) recent += window[t];
             if (recent < kWindow * kMinPerRound) {
                 // Leave the state to the kernel queued behind this one.
+                for (int r = gw; r < n; r += NW) {
+                    if (!live_at(r)) continue;
+                    const uint64_t v = upper_row_min(D, n, r, s_live);
+                    if (lane == 0) rowkey[r] = v;
+                }
                 if (w == 0) {
                     for (int q = tid; q < words; q += B) V.live[q] = s_live[q];
                     if (tid == 0) {
                         V.state[0] = (uint32_t)merges;
                         V.state[1] = (uint32_t)round;
+                        const unsigned long long left = (unsigned long long)(n - merges);
+                        atomicAdd(&ctl->rescans, left);
+                        atomicAdd(&ctl->rescan_elems, left * (left - 1) / 2);
                         atomicOr(status, kHandover);
                     }
                 }
@@ -594,18 +602,19 @@ int rounds_occupancy() {
     return blocks < 1 ? 1 : blocks;
 }
 
-hipError_t launch_rounds(float *D, int n, int link, uint32_t *status, Control *ctl, void *ws, const RoundsLayout &Lo,
-                         int G, uint64_t timeout_ticks, int flags, hipStream_t stream) {
+hipError_t launch_rounds(float *D, int n, int link, uint32_t *status, Control *ctl, uint64_t *rowkey, void *ws,
+                         const RoundsLayout &Lo, int G, uint64_t timeout_ticks, int flags, hipStream_t stream) {
     float *a0 = D;
     int a1 = n;
     int a2 = link;
     uint32_t *a3 = status;
     Control *a4 = ctl;
-    char *a5 = static_cast<char *>(ws);
-    RoundsLayout a6 = Lo;
-    uint64_t a7 = timeout_ticks;
-    int a8 = flags;
-    void *args[] = {&a0, &a1, &a2, &a3, &a4, &a5, &a6, &a7, &a8};
+    uint64_t *a5 = rowkey;
+    char *a6 = static_cast<char *>(ws);
+    RoundsLayout a7 = Lo;
+    uint64_t a8 = timeout_ticks;
+    int a9 = flags;
+    void *args[] = {&a0, &a1, &a2, &a3, &a4, &a5, &a6, &a7, &a8, &a9};
     return hipLaunchCooperativeKernel(reinterpret_cast<const void *>(&k_rounds), dim3(G), dim3(kRoundsBlock), args, 0,
                                       stream);
 }
