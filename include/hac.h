@@ -266,7 +266,7 @@ const char *hac_last_error(const hac_ctx *ctx);
  *                        loop would make next, as many as the rows' two smallest
  *                        entries prove to come next (hac_stats.rounds and
  *                        handed_over are 0 then).  0 = never, 1 = for n >= 64
- *                        (complete), 224 (averaging linkages) or 200 (single;
+ *                        (complete), 256 (averaging linkages) or 200 (single;
  *                        the default; the remaining merges go to the
  *                        one-merge-per-step kernel once rounds merge few pairs
  *                        each, on input with many equal values),

@@ -30,15 +30,15 @@ constexpr int kDeferMinGroup = 2;       // HAC_OPT_DEFER = 1: defer from this ma
 constexpr int64_t kDefaultTimeoutMs = 10000;
 // HAC_OPT_ROUNDS = 1: rounds of merges from this n on.  Measured against one
 // merge per step on one workgroup: complete n=64 0.15 / 0.18 ms, n=512 0.25 /
-// 1.65; single n=208 0.43 / 0.61 (mixture), 0.37 / 0.62 (RMSD-like), 0.67 / 0.50 (50
+// 1.65; single n=208 0.43 / 0.61 (mixture), 0.37 / 0.62 (RMSD-like), 0.62 / 0.50 (50
 // distinct values, handed over after two rounds), n=150 0.43 / 0.41.
 constexpr int kSmallComplete = 144;     // complete linkage: the small-instance kernel up to this n
 constexpr int kRoundsMinComplete = 64, kRoundsMinSingle = 200;
 constexpr int kInplaceMinN = 8192;      // complete linkage: above, rounds of few pairs go on in place (hac_contract.hip)
 // The same for the ordered rounds of the averaging linkages (rounds / one merge per
-// step, average and Ward on a mixture: n=208 0.67 / 0.66 and 0.76 / 0.70 ms, n=224 0.64 /
-// 0.71 and 0.74 / 0.74, n=256 0.74 / 0.81 and 0.82 / 0.86; RMSD-like n=224 0.54 / 0.71).
-constexpr int kOrderMinN = 224;
+// step, average and Ward on a mixture: n=208 0.67 / 0.66 and 0.76 / 0.70 ms, n=230 0.76 /
+// 0.73 and 0.84 / 0.79, n=256 0.74 / 0.81 and 0.82 / 0.86; RMSD-like n=224 0.54 / 0.71).
+constexpr int kOrderMinN = 256;
 // A running serving kernel takes all but one compute unit per XCD for as long as it
 // has jobs.  Beside it launches of a few plain workgroups complete, cooperative ones
 // and larger grids wait until it stops.  Up to this n the one-merge-per-step path

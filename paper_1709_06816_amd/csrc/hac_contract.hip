@@ -61,7 +61,7 @@ constexpr int kHandoverLeft = 96;            // the last merges are made here: t
 // what is left is priced both ways, at the last rounds' pace (eight rounds below 12
 // pairs and 96 merges left / this rule / one merge per step alone: single linkage,
 // uniform values, n = 208 1.12 / 0.49 / 0.62 ms, RMSD-like n = 320 0.82 / 0.45 / 0.99, 50
-// distinct values n = 320 1.04 / 0.97 / 0.75).
+// distinct values n = 320 1.04 / 0.87 / 0.75).
 constexpr int kSmallN = 1536;
 __device__ __forceinline__ bool cheaper_behind(int recent, int rounds, int left, int n) {
     const float merge_us = fminf(4.5f, 1.3f + 0.004f * (float)n), round_us = 12.0f, start_us = 150.0f;

@@ -443,7 +443,10 @@ __global__ __launch_bounds__(B) void k_order(OrderArgs A) {
     uint32_t TE = 0, smin = 0;  // of the last exchange: smallest exact second entry, smallest pair's value
     bool stuck = false;         // it found no merge
     // Merges per round, running mean over about 16 rounds (8 fractional bits), from
-    // what clustered points of this many items make.
+    // what clustered points of this many items make (from 16 always: constant matrix,
+    // n = 300, 1.04 ms instead of 0.85, uniform values 0.90 and 0.89).  A mean that falls
+    // faster when a round of ties makes no merge hands uniform values over too, which
+    // are better off here (n = 5000: 13.7 ms instead of 5.8).
     int pace = (int)(256.0f * fminf(16.0f, fmaxf(3.0f, 0.2f * sqrtf((float)n))));
     bool negative = false;
     const bool may_hand_over = !(A.flags & kFlagNoHandover);

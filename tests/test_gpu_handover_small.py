@@ -22,7 +22,7 @@ def _chains(n, count):
     return np.where((p % count)[:, None] == (p % count)[None, :], near, 1e4 + np.abs(x[:, None] - x[None, :])).astype(np.float32)
 
 
-@pytest.mark.parametrize("n", [224, 301, 512, 1023, 1500])
+@pytest.mark.parametrize("n", [256, 301, 512, 1023, 1500])
 def test_few_pairs_hand_over_at_once(n):
     import torch
     if not torch.cuda.is_available():
