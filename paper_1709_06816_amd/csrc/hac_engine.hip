@@ -1145,10 +1145,14 @@ __global__ __launch_bounds__(B) void k_serve(ServeHost *host, const ServeEntry *
         // registers.  s_job stays unchanged until the next claim.
         ServeEntry e;
         {
-            const uint32_t *src = reinterpret_cast<const uint32_t *>(&s_job);
-            uint32_t *dst = reinterpret_cast<uint32_t *>(&e);
+            // By bytes on both sides: through a pointer to words, the members could be
+            // read before they are written.
+            uint32_t words[sizeof(ServeEntry) / 4];
+            __builtin_memcpy(words, &s_job, sizeof words);
+#pragma unroll
             for (int q = 0; q < (int)(sizeof(ServeEntry) / 4); ++q)
-                dst[q] = (uint32_t)__builtin_amdgcn_readfirstlane((int)src[q]);
+                words[q] = (uint32_t)__builtin_amdgcn_readfirstlane((int)words[q]);
+            __builtin_memcpy(&e, words, sizeof words);
         }
         // Host memory may have changed since this kernel last read it: drop
         // cached lines before reading the job's matrix.
