@@ -314,9 +314,9 @@ int hac_set_option(hac_ctx *ctx, int32_t option, int64_t value);
  *   init_ms:           device time of the set-up kernels before it
  *   rescans:           rows whose cached minimum was recomputed
  *   rescan_elems:      matrix entries read by those recomputations (rounds of
- *                      single and complete linkage up to n = 32768: the
- *                      entries that the rounds' matrices were read and written
- *                      with, rounds_rescan_elems likewise)
+ *                      single and complete linkage up to n = 32768 that copy
+ *                      the whole matrix: the entries that it was read and
+ *                      written with, rounds_rescan_elems likewise)
  *   update_elems:      (k) entries updated by the Lance-Williams step, summed over merges
  *   workgroups:        workgroups the merge kernel ran with
  *   block:             threads per workgroup
@@ -397,8 +397,9 @@ int hac_get_stats(const hac_ctx *ctx, hac_stats *out);
  * job's matrix straight from host memory over the bus: page-locked memory in
  * place, pageable memory from a page-locked staging copy that the server's
  * host thread makes at admission.  Merge records come back the same way, into
- * page-locked memory of the server.  Jobs with n above 2048 run on a group of
- * workgroups.  A job's merge list is byte-identical to hac_run on the same
+ * page-locked memory of the server.  Jobs from n = 1024 on run on a group of
+ * workgroups while the server has workgroups to spare, from n = 4096 on
+ * otherwise.  A job's merge list is byte-identical to hac_run on the same
  * matrix, whatever else runs beside it.  A host thread of the server drives
  * admission, publication and completion; the kernel stops after a short
  * idle period and is relaunched on demand.  While it runs it holds all but a

@@ -30,6 +30,11 @@
 //   both), and store the row from LDS with its minimum taken on the way.
 //   The next row's first loads are in flight meanwhile.
 //
+// A round streams the matrix however few its pairs are.  Single linkage, which
+// has few, updates their rows and columns in place in between (kRetired); complete
+// linkage leaves such runs to the in-place engine (cheaper_in_place), and both leave
+// the last merges, or all of a run on tied input, to the one-merge-per-step kernel.
+//
 // What bounds it: memory bandwidth while m is large (read m^2, write m'^2
 // entries per round), the chain barrier -> nearest neighbours -> row ->
 // barrier below a few thousand clusters.

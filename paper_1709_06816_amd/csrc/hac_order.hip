@@ -195,8 +195,9 @@ __global__ __launch_bounds__(256) void k_row_two(const float *__restrict__ D, in
     }
 }
 
-// Merges applied together: eight per thread (16 loads in flight per lane; 16
-// spill registers at 1024 threads), at most KP.
+// Merges applied together: eight per thread (16 loads in flight per lane), at most
+// KP.  The variants of 128 to 512 columns spill 18 to 23 registers for it at 1024
+// threads, those of 1024 columns 9 to 11, of 64 columns 2.
 __host__ __device__ constexpr int group_pairs(int LC) { return ((8 * B) >> LC) < KP ? ((8 * B) >> LC) : KP; }
 
 // LDS of one workgroup: byte offsets into its dynamic LDS, constants so that

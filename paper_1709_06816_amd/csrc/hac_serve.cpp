@@ -35,7 +35,7 @@ constexpr size_t kAlign = 256;
 constexpr uint32_t kRingCap = 16384;       // entries; >= max_jobs * largest group
 constexpr int kMaxJobs = 4096;
 constexpr int kMaxGroup = 64;
-constexpr int kGroupN = 2048;              // jobs above this size run on a group
+constexpr int kGroupN = 2048;              // items per workgroup of a group (jobs from twice as many on)
 constexpr int kQuickN = 512;               // the same while the server has workgroups to spare (quick_group)
 constexpr int kPolicyMaxGroup = 16;        // largest group chosen for latency alone
 constexpr int kLargeN = 32768;             // above this, a job gets kMaxGroup workgroups (as hac_run)
@@ -162,7 +162,7 @@ int pow2_ceil(int x) {
     return p;
 }
 
-// Workgroups for a job of n items: a group above kGroupN items for latency
+// Workgroups for a job of n items: a group from 2 kGroupN items on for latency
 // (kMaxGroup above kLargeN: the n = 65536 job took 0.94 s on the 32 its LDS
 // needs, 0.77 s on 64, with the request mix's throughput unchanged), at least
 // what the per-workgroup LDS requires.
